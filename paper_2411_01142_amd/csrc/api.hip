@@ -188,6 +188,29 @@ neo_status check_decode(const void* q, const void* k_cache, const void* v_cache,
   return NEO_OK;
 }
 
+// Who runs a slice of the plan (SliceMode), from what the host knows: the
+// batch, the heads and the table's width, which bounds the lengths. Head
+// slices need whole groups of four kv heads, and pay once every compute unit
+// has a few (request, four heads) pairs with some blocks to stream: below that
+// a slice is a part of one or two pairs and the cut pairs' partials all cross
+// workgroups, where wave slices merge most of them in LDS. Measured, wave /
+// head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512, 2048]
+// tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512 of
+// U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50, 200]
+// tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52 blocks)
+// 53.9 / 54.0. A caller's slice cap is a cap on wavefronts' slices.
+constexpr int32_t kHeadPairsPerCu = 2;
+constexpr int32_t kHeadBlocksPerCu = 64;
+neo::SliceMode slice_mode(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv,
+                          int32_t mbps, int32_t cus) {
+  if (variant != NEO_VARIANT_MFMA || max_slices != 0 || hkv % neo::kHeadsPerSlice != 0)
+    return neo::kWaveSlices;
+  const int64_t pairs = (int64_t)batch * (hkv / neo::kHeadsPerSlice);
+  return pairs >= (int64_t)kHeadPairsPerCu * cus && pairs * mbps >= (int64_t)kHeadBlocksPerCu * cus
+             ? neo::kHeadSlices
+             : neo::kWaveSlices;
+}
+
 // ----------------------------------------------------------------- static scratch
 //
 // The allocation-free entry point keeps the fused kernel's cross-workgroup
@@ -302,6 +325,8 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
                               : schedule == NEO_SCHEDULE_STAGED   ? neo::kStaged
                                                                   : neo::kFused;
 
+  const neo::SliceMode mode = slice_mode(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq, cus);
+
   char* ws = static_cast<char*>(workspace);
   neo::DecodeParams p;
   p.q = static_cast<const uint16_t*>(q);
@@ -331,7 +356,7 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
   hipError_t e;
   if (sched == neo::kStaged) {
     e = neo::launch_plan(seq_lens, batch, num_kv_heads, max_blocks_per_seq, slices, min_tiles,
-                         quantum, p.xcd8, reinterpret_cast<neo::PlanHeader*>(ws + wl.hdr),
+                         quantum, p.xcd8, mode, reinterpret_cast<neo::PlanHeader*>(ws + wl.hdr),
                          reinterpret_cast<neo::SliceStart*>(ws + wl.starts),
                          reinterpret_cast<int32_t*>(ws + wl.prefix), s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "plan launch: %s", hipGetErrorString(e));
@@ -342,14 +367,14 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "event record: %s", hipGetErrorString(e));
   }
   e = variant == NEO_VARIANT_VALU ? neo::launch_decode_valu(p, group, sched, grid, s)
-                                  : neo::launch_decode_mfma(p, group, sched, grid, s);
+                                  : neo::launch_decode_mfma(p, group, mode, sched, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   if (decode_end_event) {
     e = hipEventRecord(static_cast<hipEvent_t>(decode_end_event), s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "event record: %s", hipGetErrorString(e));
   }
   if (sched != neo::kFused) {
-    e = neo::launch_combine(p, group, grid, s);
+    e = neo::launch_combine(p, group, mode, grid, s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "combine launch: %s", hipGetErrorString(e));
   }
   return ok();
@@ -435,7 +460,8 @@ neo_status neo_decode_attention_noalloc(const void* q, const void* k_cache, cons
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
   const int32_t grid = (slices + neo::kWavesPerGroup - 1) / neo::kWavesPerGroup;
-  const hipError_t e = neo::launch_decode_mfma(p, group, neo::kFused, grid, s);
+  const hipError_t e = neo::launch_decode_mfma(
+      p, group, slice_mode(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus), neo::kFused, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   return ok();
 }

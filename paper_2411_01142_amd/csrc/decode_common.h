@@ -96,6 +96,16 @@ __device__ inline void wait_all_memory() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// Between one lane's LDS write and another lane's read of it in the same
+// wavefront: the hardware keeps a wave's LDS operations in order, the compiler
+// only with this (it may otherwise give a lane that did not write the value
+// an earlier read).
+__device__ inline void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ----------------------------------------------------------------- slice geometry
 
 // Geometry of a wave-uniform slice index or position, kept in scalar
@@ -123,10 +133,14 @@ __device__ inline int partial_slot(int32_t s, int32_t slice_first, int32_t first
 // 10-25 % slower, and a small batch (4 requests of 64-512 tokens) is fastest
 // with the most slices up to one workgroup per CU (W / 8 slices: 13 % slower).
 constexpr int32_t kSmallTilesPerSlice = 2;
+// Workgroup slices: at least this many positions each.
+constexpr int32_t kMinGroupPositions = 8;
 
 __host__ __device__ inline int32_t slice_count(int32_t W, int32_t min_tiles, int32_t max_slices,
-                                               int32_t quantum) {
+                                               int32_t quantum, SliceMode mode) {
   if (W <= 0) return 0;
+  if (mode != kWaveSlices)  // four per workgroup
+    return 4 * min(max(W / kMinGroupPositions, 1), min(quantum, max_slices) / 4);
   if (min_tiles > 0) return min(max(W / min_tiles, 1), max_slices);
   const int32_t n = W >= quantum * kSmallTilesPerSlice ? quantum : max(W / kSmallTilesPerSlice, 1);
   return min(n, max_slices);
@@ -254,16 +268,40 @@ __device__ inline float sum_over_rows(float v) {
   return combine_xor32(combine_xor16(v, add), add);
 }
 
+// ----------------------------------------------------------------- cuts
+
+// Slices of the line as the wavefronts that run and merge them see them:
+// slice c starts at the geometry's slice c << shift, and this wavefront's
+// partials of it are kept under number c * mul + add.
+struct Cuts {
+  SliceGeom geo;
+  int32_t shift, mul, add;
+  __device__ int32_t first_of(int32_t c) const { return slice_start(c << shift, geo); }
+  __device__ int32_t holder(int32_t x) const { return slice_of(x, geo) >> shift; }
+  __device__ int32_t id(int32_t c) const { return c * mul + add; }
+  __device__ int32_t slot(int32_t c, int32_t first_tile) const {
+    return partial_slot(id(c), first_of(c), first_tile);
+  }
+  __device__ int32_t slot_u(int32_t c, int32_t first_tile) const {
+    return uniform(slot(c, first_tile));
+  }
+};
+// wv: the wavefront's index in its workgroup.
+__device__ inline Cuts make_cuts(const SliceGeom& geo, SliceMode mode, int32_t wv) {
+  return mode == kHeadSlices ? Cuts{geo, 2, kHeadsPerSlice, wv} : Cuts{geo, 0, 1, 0};
+}
+
 // ----------------------------------------------------------------- planning
 
 // Slice from the plan kernel's output (staged launch).
-__device__ inline SliceInfo read_plan(const DecodeParams& p, int wave) {
+template <SliceMode kMode>
+__device__ inline SliceInfo read_plan(const DecodeParams& p, int slice) {
   SliceInfo si;
-  si.geo = make_slice_geom(p.hdr->total, p.hdr->n_slices, p.xcd8 != 0);
-  if (wave >= si.geo.n) return si;
-  const SliceStart a = p.starts[wave];
+  si.geo = plan_geom(p.hdr->total, p.hdr->n_slices, p.xcd8 != 0, kMode);
+  if ((slice << slice_shift(kMode)) >= si.geo.n) return si;
+  const SliceStart a = p.starts[slice];
   si.s0 = a.pos;
-  si.s1 = p.starts[wave + 1].pos;
+  si.s1 = p.starts[slice + 1].pos;
   si.b = a.b;
   si.g = a.g;
   si.x = a.x;
@@ -293,6 +331,7 @@ constexpr int32_t kMergeCheckAhead = 3;
 // Weights of requests base + 64r + lane, r < kPlanRegs (0 past the batch), and
 // their raw lengths. Loads use a clamped index so that all of them issue before
 // any is waited on.
+template <SliceMode kMode>
 __device__ inline void load_weights(const DecodeParams& p, int base, int lane,
                                     int32_t (&w)[kPlanRegs], int32_t (&raw)[kPlanRegs]) {
 #pragma unroll
@@ -300,35 +339,39 @@ __device__ inline void load_weights(const DecodeParams& p, int base, int lane,
     raw[r] = base + r * kWave < p.batch ? p.lens[min(base + r * kWave + lane, p.batch - 1)] : 0;
 #pragma unroll
   for (int r = 0; r < kPlanRegs; ++r)
-    w[r] = (base + r * kWave + lane < p.batch) ? pair_weight(raw[r], p.mbps) : 0;
+    w[r] = (base + r * kWave + lane < p.batch) ? pair_weight(raw[r], p.mbps, kMode) : 0;
 }
 
-__device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int wave, int lane) {
+template <SliceMode kMode>
+__device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int slice, int lane) {
   SliceInfo si;
+  const int32_t hk = pairs_per_request(p.hkv, kMode);
   constexpr int kChunk = kWave * kPlanRegs;
   int32_t w[kPlanRegs], raw[kPlanRegs];
   int32_t total = 0;
   for (int base = 0; base < p.batch; base += kChunk) {
-    load_weights(p, base, lane, w, raw);
+    load_weights<kMode>(p, base, lane, w, raw);
     int32_t s = 0;
 #pragma unroll
     for (int r = 0; r < kPlanRegs; ++r) s += w[r];
     total += wave_sum_i32(s);
   }
-  const int32_t W = uniform(total * p.hkv);
+  const int32_t W = uniform(total * hk);
   si.geo = make_uniform(
-      make_slice_geom(W, slice_count(W, p.min_tiles, p.max_slices, p.slice_quantum), p.xcd8 != 0));
-  if (wave >= si.geo.n) return si;
-  si.s0 = slice_start_u(wave, si.geo);
-  si.s1 = slice_start_u(wave + 1, si.geo);
+      plan_geom(W, slice_count(W, p.min_tiles, p.max_slices, p.slice_quantum, kMode), p.xcd8 != 0,
+                kMode));
+  constexpr int kShift = slice_shift(kMode);
+  if ((slice << kShift) >= si.geo.n) return si;
+  si.s0 = slice_start_u(slice << kShift, si.geo);
+  si.s1 = slice_start_u((slice + 1) << kShift, si.geo);
 
-  // Request b holds positions [hkv*P_b, hkv*P_{b+1}) with P the weight prefix
-  // sum: the first b with hkv * P_{b+1} > s0 (no division by hkv).
+  // Request b holds positions [hk*P_b, hk*P_{b+1}) with P the weight prefix
+  // sum and hk its pairs: the first b with hk * P_{b+1} > s0 (no division).
   const int32_t s0 = si.s0;
   int32_t carry = 0;
   int32_t found_b = -1, found_p = 0, found_w = 1, found_len = 0;
   for (int base = 0; base < p.batch && found_b < 0; base += kChunk) {
-    if (p.batch > kChunk) load_weights(p, base, lane, w, raw);
+    if (p.batch > kChunk) load_weights<kMode>(p, base, lane, w, raw);
     // The register (64 requests) holding position s0, then the lane. In a
     // round of at most 64 requests the first register is it (every earlier
     // round was passed by its total); otherwise every register's sum is
@@ -345,7 +388,7 @@ __device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int wave, int la
       for (int r = 0; r < kPlanRegs; ++r) {
         const int32_t c = uniform(cs[r]);
         if (rr < 0) {
-          if (p.hkv * (carry + c) > s0) rr = r; else carry += c;
+          if (hk * (carry + c) > s0) rr = r; else carry += c;
         }
       }
       if (rr < 0) continue;  // past this round: carry holds its total
@@ -357,7 +400,7 @@ __device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int wave, int la
         }
     }
     const int32_t incl = wave_incl_scan_i32(wr);
-    const uint64_t hit = __ballot(p.hkv * (carry + incl) > s0);
+    const uint64_t hit = __ballot(hk * (carry + incl) > s0);
     const int first = __ffsll((unsigned long long)hit) - 1;
     found_b = base + rr * kWave + first;
     found_p = carry + __builtin_amdgcn_readlane(incl - wr, first);
@@ -366,7 +409,7 @@ __device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int wave, int la
   }
   // The request's weight and length come from the registers already loaded:
   // no second round trip to seq_lens before the first table row.
-  const int32_t rem = si.s0 - p.hkv * found_p;
+  const int32_t rem = si.s0 - hk * found_p;
   si.b = found_b;
   si.g = rem / found_w;
   si.x = rem % found_w;
@@ -424,7 +467,7 @@ template <int G, int GH, bool kCoherent, int kMaxBatch>
 __device__ inline void merge_pair_heads(const DecodeParams& p, const float* part_o,
                                         const float* part_lse, int32_t slot0, int32_t b,
                                         int32_t g, int h0, int32_t first_tile, int32_t c0,
-                                        int32_t c1, const SliceGeom& geo, int lane) {
+                                        int32_t c1, const Cuts& cuts, int lane) {
   constexpr int kFit = 32 / GH > 0 ? 32 / GH : 1;  // 64 registers of rows
   constexpr int kBatch = kFit < kMaxBatch ? kFit : kMaxBatch;
   auto ld = [](const float* a) -> float { return kCoherent ? load_coherent(a) : *a; };
@@ -447,7 +490,7 @@ __device__ inline void merge_pair_heads(const DecodeParams& p, const float* part
       for (int u = 0; u < kBatch; ++u) {
         if (!clamp && i0 + u >= cnt) break;  // uniform
         const int c = c0 + base + min(i0 + u, cnt - 1);
-        const int slot = partial_slot(c, slice_start_u(c, geo), first_tile) - slot0;
+        const int slot = cuts.slot_u(c, first_tile) - slot0;
 #pragma unroll
         for (int h = 0; h < GH; ++h) {
           const float2 v = ld2(part_o + ((size_t)slot * G + h0 + h) * kHeadDim + d);
@@ -458,7 +501,7 @@ __device__ inline void merge_pair_heads(const DecodeParams& p, const float* part
     };
     load_rows(0, true);
     const int mine = c0 + base + (lane < cnt ? lane : 0);
-    const int my_slot = partial_slot(mine, slice_start(mine, geo), first_tile) - slot0;
+    const int my_slot = cuts.slot(mine, first_tile) - slot0;
     // Every head's log-sum-exp is loaded before any cross-lane step, so the
     // loads share one round trip.
     float lse_h[GH];
@@ -507,11 +550,11 @@ template <int G, bool kCoherent, int kMaxBatch = 16, int GH = G>
 __device__ inline void merge_pair(const DecodeParams& p, const float* part_o,
                                   const float* part_lse, int32_t slot0, int32_t b, int32_t g,
                                   int32_t first_tile, int32_t c0, int32_t c1,
-                                  const SliceGeom& geo, int lane) {
+                                  const Cuts& cuts, int lane) {
   static_assert(G % GH == 0, "head passes must tile the group");
   for (int h0 = 0; h0 < G; h0 += GH)
     merge_pair_heads<G, GH, kCoherent, kMaxBatch>(p, part_o, part_lse, slot0, b, g, h0,
-                                                  first_tile, c0, c1, geo, lane);
+                                                  first_tile, c0, c1, cuts, lane);
 }
 
 // The merge of a pair with exactly two contributors, partial slots sa (the
@@ -549,17 +592,23 @@ __device__ inline void merge_two(const DecodeParams& p, const float* part_o,
 
 // Fused launch: after writing its partial for a cut pair, a slice counts itself
 // in the pair's counter; the slice that completes the count merges the pair
-// (returns true) and resets the counter to zero for the next call.
-__device__ inline bool arrive_last(const DecodeParams& p, int32_t c0, int32_t c1, int lane) {
-  wait_all_memory();  // this slice's partial has reached the coherence point
+// (returns true) and resets the counter to zero for the next call. id: the
+// counter, the one of the pair's first slice; k contributors.
+__device__ inline int32_t count_arrival(const DecodeParams& p, int32_t id, int lane) {
   int32_t old = 0;
   if (lane == 0)
-    old = __hip_atomic_fetch_add(p.counters + c0, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  old = __builtin_amdgcn_readlane(old, 0);
-  if (old != c1 - c0) return false;
+    old = __hip_atomic_fetch_add(p.counters + id, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return old;  // in lane 0
+}
+__device__ inline bool is_last(const DecodeParams& p, int32_t id, int32_t k, int32_t old, int lane) {
+  if (__builtin_amdgcn_readlane(old, 0) != k - 1) return false;
   if (lane == 0)
-    __hip_atomic_store(p.counters + c0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.counters + id, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
+}
+__device__ inline bool arrive_last(const DecodeParams& p, int32_t id, int32_t k, int lane) {
+  wait_all_memory();  // this slice's partial has reached the coherence point
+  return is_last(p, id, k, count_arrival(p, id, lane), lane);
 }
 
 // ----------------------------------------------------------------- the driver
@@ -589,6 +638,81 @@ struct GroupMergeOf<G, false> {
   };
 };
 
+// Two-kernel launch: the plan of this slice (and of the whole line, by slice
+// 0), recorded for the combine kernel by one lane.
+template <SliceMode kMode>
+__device__ inline void record_plan(const DecodeParams& p, const SliceInfo& si, int32_t slice) {
+  constexpr int kShift = slice_shift(kMode);
+  if ((slice << kShift) < si.geo.n) {
+    SliceStart a;
+    a.pos = si.s0;
+    a.b = si.b;
+    a.g = si.g;
+    a.x = si.x;
+    a.nb = blocks_of(p.lens[si.b], p.mbps);
+    a.pad[0] = a.pad[1] = a.pad[2] = 0;
+    p.starts[slice] = a;
+  }
+  if (slice == 0) {
+    SliceStart e;
+    e.pos = si.geo.W;
+    e.b = p.batch;
+    e.g = e.x = e.nb = 0;
+    e.pad[0] = e.pad[1] = e.pad[2] = 0;
+    p.starts[si.geo.n >> kShift] = e;
+    PlanHeader h;
+    h.total = si.geo.W;
+    h.n_slices = si.geo.n;
+    h.batch = p.batch;
+    h.pad = 0;
+    *p.hdr = h;
+  }
+}
+
+// Counts this wave's share of a pair, written to gm, and merges the pair if it
+// is the last of the workgroup's waves c0 .. c1 (wave slices) to do so.
+template <int G>
+__device__ inline void merge_in_group(const DecodeParams& p, GroupMerge<G>& gm, int32_t first_slice,
+                                      int32_t b, int32_t g, int32_t first_tile, int32_t c0,
+                                      int32_t c1, const Cuts& cuts, int lane) {
+  constexpr int kHeads = GroupMerge<G>::kHeadsPerPass;
+  const int32_t slot0 = 2 * first_slice;
+  // LDS operations of a wave complete in order: once this wave's partial
+  // writes are done (lgkmcnt 0), its count follows them, and a wave that reads
+  // the count after it sees the partial. Waiting on LDS only: an
+  // acquire-release atomic would also wait for every vector memory operation
+  // in flight (vmcnt 0), including the tile loads queued behind other waves'
+  // loads, which costs up to a round trip.
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
+  int32_t old = 0;
+  if (lane == 0)
+    old = __hip_atomic_fetch_add(&gm.count[c0 - first_slice], 1, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+  old = __builtin_amdgcn_readlane(old, 0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  if (old != c1 - c0) return;
+  if (c1 == c0 + 1) {
+    merge_two<G, false, kHeads>(p, &gm.o[0][0], &gm.lse[0][0], b, g,
+                                cuts.slot_u(c0, first_tile) - slot0,
+                                cuts.slot_u(c1, first_tile) - slot0, lane);
+  } else {
+    merge_pair<G, false, 1, kHeads>(p, &gm.o[0][0], &gm.lse[0][0], slot0, b, g, first_tile, c0,
+                                    c1, cuts, lane);
+  }
+}
+
+// Merges the workspace partials of cut pair (b, kv head g), slices c0 .. c1.
+template <int G>
+__device__ inline void merge_cut(const DecodeParams& p, int32_t b, int32_t g, int32_t first_tile,
+                                 int32_t c0, int32_t c1, const Cuts& cuts, int lane) {
+  if (c1 == c0 + 1)
+    merge_two<G, true>(p, p.part_o, p.part_lse, b, g, cuts.slot_u(c0, first_tile),
+                       cuts.slot_u(c1, first_tile), lane);
+  else
+    merge_pair<G, true>(p, p.part_o, p.part_lse, 0, b, g, first_tile, c0, c1, cuts, lane);
+}
+
 // Family provides: Tile, State, Q, Shared; load_q, init, load_tile, step, write.
 // PF tiles are in flight ahead of the one being computed.
 template <class F, int G, int PF, Schedule kSched>
@@ -602,7 +726,8 @@ __device__ inline void decode_driver(const DecodeParams& p) {
   // Slices of this workgroup: first_slice .. first_slice + kWavesPerGroup - 1.
   const int32_t first_slice = blockIdx.x * kWavesPerGroup;
   __shared__ typename GroupMergeOf<G, kMergeHere>::type gm;
-  const SliceInfo si = kSched == kStaged ? read_plan(p, wave) : plan_in_wave(p, wave, lane);
+  const SliceInfo si = kSched == kStaged ? read_plan<kWaveSlices>(p, wave)
+                                          : plan_in_wave<kWaveSlices>(p, wave, lane);
   zero_empty_rows(p, wave, nwaves, lane, len0);
   // Merges through LDS pay when slices are long enough to hold cut segments
   // of several tiles; for tiny slices the barrier that clears the counters
@@ -616,34 +741,9 @@ __device__ inline void decode_driver(const DecodeParams& p) {
       __syncthreads();
     }
   }
-  if (kSched == kTwoKernel && lane == 0) {
-    // Record the plan for the combine kernel.
-    if (wave < si.geo.n) {
-      SliceStart a;
-      a.pos = si.s0;
-      a.b = si.b;
-      a.g = si.g;
-      a.x = si.x;
-      a.nb = blocks_of(p.lens[si.b], p.mbps);
-      a.pad[0] = a.pad[1] = a.pad[2] = 0;
-      p.starts[wave] = a;
-    }
-    if (wave == 0) {
-      SliceStart e;
-      e.pos = si.geo.W;
-      e.b = p.batch;
-      e.g = e.x = e.nb = 0;
-      e.pad[0] = e.pad[1] = e.pad[2] = 0;
-      p.starts[si.geo.n] = e;
-      PlanHeader h;
-      h.total = si.geo.W;
-      h.n_slices = si.geo.n;
-      h.batch = p.batch;
-      h.pad = 0;
-      *p.hdr = h;
-    }
-  }
+  if (kSched == kTwoKernel && lane == 0) record_plan<kWaveSlices>(p, si, wave);
   if (wave >= si.geo.n) return;
+  const Cuts cuts = make_cuts(si.geo, kWaveSlices, wv);
 
   __shared__ typename F::Shared shared[kWavesPerGroup];
   typename F::Shared& sh = shared[wv];
@@ -676,7 +776,7 @@ __device__ inline void decode_driver(const DecodeParams& p) {
       continue;
     }
     const int32_t pair_base = pos - x;
-    const int32_t cost = pair_cost(nb);
+    const int32_t cost = pair_cost(nb, kWaveSlices);
     const int32_t first_tile = pair_base + cost;  // position of block 0
     const int32_t j = max(0, x - cost);
     const int32_t jend = min(nb, si.s1 - first_tile);
@@ -733,8 +833,8 @@ __device__ inline void decode_driver(const DecodeParams& p) {
     // (computed here, where their latency hides behind the first tile's
     // round trip; after the tiles it delayed every cut segment's result).
     const bool cut = j > 0 || jend < nb;
-    const int32_t c0 = cut ? slice_of_u(first_tile, si.geo) : 0;
-    const int32_t c1 = cut ? slice_of_u(first_tile + nb - 1, si.geo) : 0;
+    const int32_t c0 = cut ? uniform(cuts.holder(first_tile)) : 0;
+    const int32_t c1 = cut ? uniform(cuts.holder(first_tile + nb - 1)) : 0;
 
     // Fused launch, last pair of this slice cut with exactly one later slice
     // (the next one), which handles its share of the pair first: if it has
@@ -773,50 +873,23 @@ __device__ inline void decode_driver(const DecodeParams& p) {
       if constexpr (kMergeHere && F::kFastMerge) {
         if (lane == 0)
           __hip_atomic_store(p.counters + wave, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t nxt = wave + 1;
-        const int slot = partial_slot(nxt, slice_start_u(nxt, si.geo), first_tile);
+        const int slot = cuts.slot_u(wave + 1, first_tile);
         F::merge_write(st, p.part_o + (size_t)slot * G * kHeadDim, p.part_lse + slot * G,
                        p.out + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
       }
     } else if (group_merge && c0 >= first_slice && c1 < first_slice + kWavesPerGroup) {
       if constexpr (kMergeHere) {
         // Every contributor is a wave of this workgroup: merge through LDS.
-        const int32_t slot0 = 2 * first_slice;
-        constexpr int kLdsMergeHeads = GroupMerge<G>::kHeadsPerPass;
-        const int ls = partial_slot(wave, si.s0, first_tile) - slot0;
+        const int ls = partial_slot(wave, si.s0, first_tile) - 2 * first_slice;
         F::template write<false>(st, gm.o[ls], gm.lse[ls], lane);
-        // LDS operations of a wave complete in order: once this wave's
-        // partial writes are done (lgkmcnt 0), its count follows them, and a
-        // wave that reads the count after it sees the partial. Waiting on LDS
-        // only: an acquire-release atomic would also wait for every vector
-        // memory operation in flight (vmcnt 0), including the empty tile load
-        // queued behind other waves' loads, which costs up to a round trip.
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkmcnt0);
-        int32_t old = 0;
-        if (lane == 0)
-          old = __hip_atomic_fetch_add(&gm.count[c0 - first_slice], 1, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-        old = __builtin_amdgcn_readlane(old, 0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (old == c1 - c0) {
-          if (c1 == c0 + 1) {
-            merge_two<G, false, kLdsMergeHeads>(p, &gm.o[0][0], &gm.lse[0][0], b, g,
-                                partial_slot(c0, slice_start_u(c0, si.geo), first_tile) - slot0,
-                                partial_slot(c1, slice_start_u(c1, si.geo), first_tile) - slot0,
-                                lane);
-          } else {
-            merge_pair<G, false, 1, kLdsMergeHeads>(p, &gm.o[0][0], &gm.lse[0][0], slot0, b, g,
-                                                    first_tile, c0, c1, si.geo, lane);
-          }
-        }
+        merge_in_group<G>(p, gm, first_slice, b, g, first_tile, c0, c1, cuts, lane);
       }
     } else {
       const int slot = partial_slot(wave, si.s0, first_tile);
       F::template write<kMergeHere>(st, p.part_o + (size_t)slot * G * kHeadDim,
                                 p.part_lse + slot * G, lane);
       if (kMergeHere) {
-        if (arrive_last(p, c0, c1, lane)) {
+        if (arrive_last(p, c0, c1 - c0 + 1, lane)) {
           const Pending rec{b, g, first_tile, c0, c1};
           if (npend == 0) pend0 = rec; else pend1 = rec;
           ++npend;
@@ -834,15 +907,8 @@ __device__ inline void decode_driver(const DecodeParams& p) {
   }
   if (kMergeHere) {
     for (int i = 0; i < npend; ++i) {
-      const Pending q = i == 0 ? pend0 : pend1;
-      if (q.c1 == q.c0 + 1) {
-        merge_two<G, true>(p, p.part_o, p.part_lse, q.b, q.g,
-                           partial_slot(q.c0, slice_start_u(q.c0, si.geo), q.first),
-                           partial_slot(q.c1, slice_start_u(q.c1, si.geo), q.first), lane);
-      } else {
-        merge_pair<G, true>(p, p.part_o, p.part_lse, 0, q.b, q.g, q.first, q.c0, q.c1, si.geo,
-                            lane);
-      }
+      const Pending r = i == 0 ? pend0 : pend1;
+      merge_cut<G>(p, r.b, r.g, r.first, r.c0, r.c1, cuts, lane);
     }
   }
 }

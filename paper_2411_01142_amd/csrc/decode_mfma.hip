@@ -21,7 +21,7 @@
 // each lane keeps a partial sum of its own tokens' weights. The weights enter
 // the second product as bf16 hi + lo halves (two products), which keeps ~16
 // mantissa bits of each weight.
-#include "decode_common.h"
+#include "decode_stream.h"
 
 namespace neo {
 namespace {
@@ -44,15 +44,14 @@ struct MfmaFamily {
     int unused;
   };
   static constexpr bool kFastMerge = true;  // provides merge_write
-
+  // Columns past the group repeat its first head: their results are never
+  // written, and a loaded fragment needs no select (which would wait for it).
   __device__ static void load_q(Q& q, const uint16_t* __restrict__ qpair, int lane) {
     const int col = lane & 15, rq = lane >> 4;
     const uint16_t* row = qpair + (col < G ? col : 0) * kHeadDim;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(row + kPiece * (4 * kb + rq));
-      q.f[kb] = (col < G) ? v : bf16x8_t{};
-    }
+    for (int kb = 0; kb < 4; ++kb)
+      q.f[kb] = *reinterpret_cast<const bf16x8_t*>(row + kPiece * (4 * kb + rq));
   }
 
   __device__ static void init(State& st) {
@@ -191,10 +190,68 @@ struct MfmaFamily {
       }
     }
   }
+
+  // The state normalised to output rows; returns each head's natural-log
+  // log-sum-exp (in the lanes of its column).
+  __device__ static float normalise(State& st) {
+    const float lt = sum_over_rows(st.l);
+    const float inv = 1.f / lt;
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) st.acc[mb] *= inv;
+    return (st.m + __log2f(lt)) * kLn2;
+  }
+
+  // Normalised state to a staging slot in LDS: [G][128] floats whose 16-byte
+  // words are permuted within each row (word c of row h at c ^ h), so that the
+  // rows' writes, 512 bytes apart, fall into different banks.
+  __device__ static void stage(const State& st, float* __restrict__ slot, int lane) {
+    const int col = lane & 15, rq = lane >> 4;
+    if (col < G) {
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+        *reinterpret_cast<f32x4_t*>(slot + col * kHeadDim + 4 * ((4 * mb + rq) ^ col)) = st.acc[mb];
+    }
+  }
+
+  // The pair's two-contributor merge done in registers: this slice's share
+  // (normalised, with its log-sum-exp la) first, then the other slice's
+  // complete partial (device-coherent loads); the same arithmetic as
+  // merge_two_values on the stored partials, so the output bits are the same.
+  __device__ static void merge_in_place(State& st, float la, const float* __restrict__ other_rows,
+                                        const float* __restrict__ other_lse, int lane) {
+    const int col = lane & 15, rq = lane >> 4;
+    if (col < G) {
+      // Rounded exactly as the stored log-sum-exp: the empty asm makes la an
+      // opaque value, so the compiler cannot fuse its multiply with the
+      // subtraction of the max below (the merge must see the same value as the
+      // merge of stored partials).
+      asm volatile("" : "+v"(la));
+      const float lb = load_coherent(other_lse + col);
+      const float* ob = other_rows + col * kHeadDim + 4 * rq;
+      float2 o2[8][2];
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        o2[mb][0] = load_coherent2(ob + 16 * mb);
+        o2[mb][1] = load_coherent2(ob + 16 * mb + 2);
+      }
+      const float m = fmaxf(la, lb);
+      const float wa = __expf(la - m), wb = __expf(lb - m);
+      const float inv2 = 1.f / (wa + wb);
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        const float obv[4] = {o2[mb][0].x, o2[mb][0].y, o2[mb][1].x, o2[mb][1].y};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          st.acc[mb][i] = fmaf(wb, obv[i], wa * st.acc[mb][i]) * inv2;
+      }
+    }
+  }
 };
 
-template <int G, Schedule kSched>
-__global__ __launch_bounds__(kWave * kWavesPerGroup, 2) void decode_mfma_kernel(
+// Head slices run one workgroup per compute unit (their LDS); the registers of
+// a whole SIMD are theirs.
+template <int G, SliceMode kMode, Schedule kSched>
+__global__ __launch_bounds__(kWave * kWavesPerGroup, kMode == kHeadSlices ? 1 : 2) void decode_mfma_kernel(
     const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
   // The first step of every wave reads the request lengths: the arguments it
   // needs for that come first and separately, so that they can arrive in
@@ -204,33 +261,50 @@ __global__ __launch_bounds__(kWave * kWavesPerGroup, 2) void decode_mfma_kernel(
   p.batch = batch;
   p.hkv = hkv;
   p.mbps = mbps;
-  // One tile in flight ahead of the one being computed: with 4 waves on every
-  // CU that keeps HBM saturated; deeper prefetch measured equal or slower
-  // (more requests in flight lower the HBM efficiency).
-  decode_driver<MfmaFamily<G>, G, 1, kSched>(p);
+  if constexpr (kMode == kHeadSlices) {
+    stream_driver<MfmaFamily<G>, G, kSched>(p);
+  } else {
+    // One tile in flight ahead of the one being computed: with 4 waves on every
+    // CU that keeps HBM saturated; deeper prefetch measured equal or slower
+    // (more requests in flight lower the HBM efficiency).
+    decode_driver<MfmaFamily<G>, G, 1, kSched>(p);
+  }
 }
 
-template <int G>
+template <int G, SliceMode kMode>
 hipError_t launch_g(const DecodeParams& p, Schedule sched, int32_t grid, hipStream_t stream) {
   const dim3 block(kWave * kWavesPerGroup);
   switch (sched) {
-    case kStaged: decode_mfma_kernel<G, kStaged><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p); break;
-    case kFused: decode_mfma_kernel<G, kFused><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p); break;
-    case kTwoKernel: decode_mfma_kernel<G, kTwoKernel><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p); break;
+    case kStaged:
+      decode_mfma_kernel<G, kMode, kStaged><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+      break;
+    case kFused:
+      decode_mfma_kernel<G, kMode, kFused><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+      break;
+    case kTwoKernel:
+      decode_mfma_kernel<G, kMode, kTwoKernel><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+      break;
   }
   return hipGetLastError();
 }
 
+template <int G>
+hipError_t launch_mode(const DecodeParams& p, SliceMode mode, Schedule sched, int32_t grid,
+                       hipStream_t stream) {
+  return mode == kHeadSlices ? launch_g<G, kHeadSlices>(p, sched, grid, stream)
+                             : launch_g<G, kWaveSlices>(p, sched, grid, stream);
+}
+
 }  // namespace
 
-hipError_t launch_decode_mfma(const DecodeParams& p, int32_t group, Schedule sched,
+hipError_t launch_decode_mfma(const DecodeParams& p, int32_t group, SliceMode mode, Schedule sched,
                               int32_t grid, hipStream_t stream) {
   switch (group) {
-    case 1: return launch_g<1>(p, sched, grid, stream);
-    case 2: return launch_g<2>(p, sched, grid, stream);
-    case 4: return launch_g<4>(p, sched, grid, stream);
-    case 8: return launch_g<8>(p, sched, grid, stream);
-    case 16: return launch_g<16>(p, sched, grid, stream);
+    case 1: return launch_mode<1>(p, mode, sched, grid, stream);
+    case 2: return launch_mode<2>(p, mode, sched, grid, stream);
+    case 4: return launch_mode<4>(p, mode, sched, grid, stream);
+    case 8: return launch_mode<8>(p, mode, sched, grid, stream);
+    case 16: return launch_mode<16>(p, mode, sched, grid, stream);
     default: return hipErrorInvalidValue;
   }
 }

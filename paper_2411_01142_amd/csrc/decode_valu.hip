@@ -43,12 +43,6 @@ __device__ inline float dot8(const u32x4_t& a, const u32x4_t& b) {
 __device__ inline float bf16_lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xFFFF0000u); }
 
-__device__ inline void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int G>
 struct ValuFamily {
   struct Tile {
@@ -67,7 +61,6 @@ struct ValuFamily {
     float p[G * kBlock];  // softmax weights of the current tile, [head][token]
   };
   static constexpr bool kFastMerge = false;  // no merge_write: the general path merges
-
 
   __device__ static void load_q(Q& q, const uint16_t* __restrict__ qpair, int lane) {
     const int c = lane & 15;

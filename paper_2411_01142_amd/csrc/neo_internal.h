@@ -38,10 +38,29 @@ constexpr int32_t kPairCostShort = 1;
 constexpr int32_t kPairCostLong = 3;
 constexpr int32_t kShortPairBlocks = 4;
 constexpr int32_t kLongPairBlocks = 32;
-__host__ __device__ inline int32_t pair_cost(int32_t nb) {
+
+// How the tiles are laid out on the weighted line and who runs a slice of it.
+//  kWaveSlices: a pair is (request, kv head); one slice per wavefront.
+//  kHeadSlices: a pair is (request, four kv heads); one slice per workgroup,
+//    whose four wavefronts walk the same blocks together, one head each.
+enum SliceMode { kWaveSlices = 0, kHeadSlices = 1 };
+constexpr int kHeadsPerSlice = 4;  // kHeadSlices: kv heads of a pair, one per wavefront
+// Head slices stream across pair ends, which costs a pair little more than its
+// arithmetic.
+constexpr int32_t kPairCostHeads = 1;
+
+__host__ __device__ inline int32_t pair_cost(int32_t nb, SliceMode mode) {
+  if (mode == kHeadSlices) return kPairCostHeads;
   return nb >= kLongPairBlocks ? kPairCostLong
                                : (nb >= kShortPairBlocks ? kPairCost : kPairCostShort);
 }
+// Pairs per request.
+__host__ __device__ inline int32_t pairs_per_request(int32_t hkv, SliceMode mode) {
+  return mode == kHeadSlices ? hkv / kHeadsPerSlice : hkv;
+}
+// The slice geometry counts in slices of one wavefront; a workgroup's slice is
+// four of them.
+__host__ __device__ constexpr int slice_shift(SliceMode mode) { return mode == kWaveSlices ? 0 : 2; }
 
 // Slice geometry of the weighted line: W positions cut into n slices. Slice s
 // owns [floor(C(s) W / C(n)), floor(C(s+1) W / C(n))), C(s) being the units of
@@ -67,10 +86,15 @@ __host__ __device__ inline int32_t pair_cost(int32_t nb) {
 constexpr int32_t kXcdEvenUnits = 34;
 constexpr int32_t kXcdOddUnits = 30;
 constexpr int32_t kXcdWeightMinTiles = 16;
+// Head slices: 33 : 31. With 34 : 30 the even XCDs end 10-45 us after the odd
+// ones on the 70B layer (mean end 652-667 against 614-643 us), with equal
+// slices 35 us before them, with 33 : 31 within 10 us: 672, 683 and 666 us a
+// call; skewed mix 270, 272, 264; lognormal mix over dense caches 298, 296, 293.
+constexpr int32_t kXcdEvenUnitsHeads = 33;
 constexpr int32_t kXcdPeriodUnits = 4 * (kXcdEvenUnits + kXcdOddUnits);  // 8 slices
 struct SliceGeom {
   int32_t W, n;      // positions and slices, 0 < n <= min(W, NEO_MAX_SLICES) (n = 0: no slices)
-  int32_t weighted;  // 1: slices weighed by XCD
+  int32_t weighted;  // 0, or the units of a slice on an even XCD
   int32_t cn;        // C(n)
   int32_t a, r;      // W = a C(n) + r
   float r_over_cn;   // r / C(n)
@@ -80,11 +104,12 @@ static_assert((int64_t)(NEO_MAX_SLICES / 8) * kXcdPeriodUnits < ((int64_t)1 << 2
               "C(s) must be exact in fp32");
 
 // xcd8: the device has eight XCDs.
-__host__ __device__ inline SliceGeom make_slice_geom(int32_t W, int32_t n, bool xcd8) {
+__host__ __device__ inline SliceGeom make_slice_geom(int32_t W, int32_t n, bool xcd8,
+                                                      int32_t even_units = kXcdEvenUnits) {
   SliceGeom g;
   g.W = W;
   g.n = n;
-  g.weighted = xcd8 && n > 0 && n % 8 == 0 && W / kXcdWeightMinTiles >= n;
+  g.weighted = xcd8 && n > 0 && n % 8 == 0 && W / kXcdWeightMinTiles >= n ? even_units : 0;
   g.cn = g.weighted ? (n / 8) * kXcdPeriodUnits : n;
   g.a = g.cn > 0 ? W / g.cn : 0;
   g.r = W - g.a * g.cn;
@@ -95,9 +120,8 @@ __host__ __device__ inline SliceGeom make_slice_geom(int32_t W, int32_t n, bool 
 // C(s), for 0 <= s <= n.
 __host__ __device__ inline int32_t slice_units(int32_t s, const SliceGeom& g) {
   if (!g.weighted) return s;
-  const int32_t k = s & 7;
-  return (s >> 3) * kXcdPeriodUnits +
-         (k < 4 ? k * kXcdEvenUnits : 4 * kXcdEvenUnits + (k - 4) * kXcdOddUnits);
+  const int32_t k = s & 7, even = g.weighted, odd = kXcdPeriodUnits / 4 - even;
+  return (s >> 3) * kXcdPeriodUnits + (k < 4 ? k * even : 4 * even + (k - 4) * odd);
 }
 // First position of slice s, for 0 <= s <= n.
 __host__ __device__ inline int32_t slice_start(int32_t s, const SliceGeom& g) {
@@ -120,6 +144,11 @@ __host__ __device__ inline int32_t slice_of(int32_t x, const SliceGeom& g) {
   const bool down = slice_start(s, g) > x;
   const bool up = s + 1 < g.n && slice_start(s + 1, g) <= x;
   return down ? s - 1 : (up ? s + 1 : s);
+}
+
+// The geometry of a plan.
+__host__ __device__ inline SliceGeom plan_geom(int32_t W, int32_t n, bool xcd8, SliceMode mode) {
+  return make_slice_geom(W, n, xcd8, mode == kHeadSlices ? kXcdEvenUnitsHeads : kXcdEvenUnits);
 }
 
 struct alignas(16) PlanHeader {
@@ -179,9 +208,9 @@ __host__ __device__ inline int32_t blocks_of(int32_t L, int32_t mbps) {
   return (clamp_len(L, mbps) + kBlock - 1) / kBlock;
 }
 // Positions of each (request, kv head) pair of a request with this length.
-__host__ __device__ inline int32_t pair_weight(int32_t L, int32_t mbps) {
+__host__ __device__ inline int32_t pair_weight(int32_t L, int32_t mbps, SliceMode mode) {
   const int32_t nb = blocks_of(L, mbps);
-  return nb > 0 ? nb + pair_cost(nb) : 0;
+  return nb > 0 ? nb + pair_cost(nb, mode) : 0;
 }
 
 struct DecodeParams {
@@ -207,13 +236,14 @@ struct DecodeParams {
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_plan(const int32_t* lens, int32_t batch, int32_t hkv, int32_t mbps,
                        int32_t max_slices, int32_t min_tiles, int32_t quantum, int32_t xcd8,
-                       PlanHeader* hdr, SliceStart* starts, int32_t* prefix, hipStream_t stream);
+                       SliceMode mode, PlanHeader* hdr, SliceStart* starts, int32_t* prefix, hipStream_t stream);
 hipError_t launch_decode_valu(const DecodeParams& p, int32_t group, Schedule sched,
                               int32_t grid, hipStream_t stream);
-hipError_t launch_decode_mfma(const DecodeParams& p, int32_t group, Schedule sched,
+hipError_t launch_decode_mfma(const DecodeParams& p, int32_t group, SliceMode mode, Schedule sched,
                               int32_t grid, hipStream_t stream);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t stream);
-hipError_t launch_combine(const DecodeParams& p, int32_t group, int32_t grid, hipStream_t stream);
+hipError_t launch_combine(const DecodeParams& p, int32_t group, SliceMode mode, int32_t grid,
+                          hipStream_t stream);
 hipError_t launch_gather(const uint16_t* cache, int32_t is_v, const int32_t* table,
                          const int32_t* lens, const int32_t* offsets, int32_t batch,
                          int32_t mbps, int32_t hkv, int32_t head_dim, int32_t block_size,

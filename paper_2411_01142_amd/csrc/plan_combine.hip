@@ -21,18 +21,19 @@ constexpr int kPlanLdsBatch = 8192;
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
     const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps,
-    int32_t max_slices, int32_t min_tiles, int32_t quantum, int32_t xcd8,
-    PlanHeader* __restrict__ hdr,
-    SliceStart* __restrict__ starts, int32_t* __restrict__ prefix) {
+    int32_t max_slices, int32_t min_tiles, int32_t quantum, int32_t xcd8, SliceMode mode,
+    PlanHeader* __restrict__ hdr, SliceStart* __restrict__ starts, int32_t* __restrict__ prefix) {
   __shared__ int32_t sums[kPlanThreads];
   __shared__ int32_t sprefix[kPlanLdsBatch + 1];
   const bool in_lds = batch <= kPlanLdsBatch;
   const int tid = threadIdx.x;
+  const int32_t hk = pairs_per_request(hkv, mode);
+  const int shift = slice_shift(mode);
   const int per = (batch + kPlanThreads - 1) / kPlanThreads;
   const int b0 = min(batch, tid * per);
   const int b1 = min(batch, b0 + per);
   int32_t local = 0;
-  for (int b = b0; b < b1; ++b) local += pair_weight(lens[b], mbps);
+  for (int b = b0; b < b1; ++b) local += pair_weight(lens[b], mbps, mode);
   sums[tid] = local;
   __syncthreads();
   for (int off = 1; off < kPlanThreads; off <<= 1) {
@@ -43,33 +44,33 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
   }
   int32_t run = tid == 0 ? 0 : sums[tid - 1];
   for (int b = b0; b < b1; ++b) {
-    if (in_lds) sprefix[b] = run * hkv;
-    else prefix[b] = run * hkv;
-    run += pair_weight(lens[b], mbps);
+    if (in_lds) sprefix[b] = run * hk;
+    else prefix[b] = run * hk;
+    run += pair_weight(lens[b], mbps, mode);
   }
-  const int32_t total = sums[kPlanThreads - 1] * hkv;
+  const int32_t total = sums[kPlanThreads - 1] * hk;
   __syncthreads();
   const int32_t* pre = in_lds ? sprefix : prefix;
 
-  const int32_t n = slice_count(total, min_tiles, max_slices, quantum);
-  const SliceGeom geo = make_slice_geom(total, n, xcd8 != 0);
-  for (int s = tid; s <= n; s += kPlanThreads) {
+  const int32_t n = slice_count(total, min_tiles, max_slices, quantum, mode);
+  const SliceGeom geo = plan_geom(total, n, xcd8 != 0, mode);
+  for (int s = tid; s <= n >> shift; s += kPlanThreads) {
     SliceStart st;
     st.pad[0] = st.pad[1] = st.pad[2] = 0;
-    if (s == n) {
+    if (s == n >> shift) {
       st.pos = total;
       st.b = batch;
       st.g = 0;
       st.x = 0;
       st.nb = 0;
     } else {
-      const int32_t pos = slice_start(s, geo);
+      const int32_t pos = slice_start(s << shift, geo);
       int lo = 0, hi = batch - 1;  // largest b with pre[b] <= pos
       while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
         if (pre[mid] <= pos) lo = mid; else hi = mid - 1;
       }
-      const int32_t w = pair_weight(lens[lo], mbps);
+      const int32_t w = pair_weight(lens[lo], mbps, mode);
       const int32_t r = pos - pre[lo];
       st.pos = pos;
       st.b = lo;
@@ -95,24 +96,29 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(
 // pair whose first tile lies in slice s - 1, that boundary is the first to cut
 // the pair and the wave merges it. Every contributing slice stored its part
 // normalised, with its log-sum-exp.
-template <int G>
+template <int G, SliceMode kMode>
 __global__ __launch_bounds__(kWave * kWavesPerGroup) void combine_kernel(DecodeParams p) {
+  constexpr int kShift = slice_shift(kMode);
+  constexpr int kLast = (NEO_MAX_SLICES >> kShift) - 1;  // the last slice any plan has
   const int lane = threadIdx.x & (kWave - 1);
-  const int s = blockIdx.x * kWavesPerGroup + (threadIdx.x >> 6) + 1;
-  if (s > NEO_MAX_SLICES) return;
+  const int wv = threadIdx.x >> 6;
+  // Head slices: the four wavefronts share the boundary, a head each.
+  const int s = (kMode == kHeadSlices ? blockIdx.x : blockIdx.x * kWavesPerGroup + wv) + 1;
+  if (s > kLast + 1) return;
   // The header and this boundary's record are loaded together (the record
   // array always holds NEO_MAX_SLICES + 1 entries; stale ones are not used).
   const SliceStart a = p.starts[s];
   const int32_t W = p.hdr->total;
   const int32_t n = p.hdr->n_slices;
   // A pair cut at this boundary nearly always has exactly two contributors:
-  // slice s-1's end-cut segment (slot 2s-1) and slice s's first segment (slot
-  // 2s). Their log-sum-exps and rows are loaded in the same round trip as the
-  // record (all slots exist whatever the plan; unused values are ignored).
-  // (s <= NEO_MAX_SLICES here; the slots read are clamped below 2 NEO_MAX_SLICES,
-  // s = NEO_MAX_SLICES being a boundary no plan has.)
+  // slice s-1's end-cut segment (its odd slot) and slice s's first segment (its
+  // even slot). Their log-sum-exps and rows are loaded in the same round trip
+  // as the record (all slots exist whatever the plan; unused values are
+  // ignored; s = kLast + 1 is a boundary no plan has, and is clamped).
   const int d = 2 * lane;
-  const int sa = 2 * min(s, NEO_MAX_SLICES - 1) - 1, sb = sa + 1;
+  const Cuts at = make_cuts(SliceGeom{}, kMode, wv);
+  const int sr = min(s, kLast);
+  const int sa = 2 * at.id(sr - 1) + 1, sb = 2 * at.id(sr);
   float la[G], lb[G];
   float2 oa[G], ob[G];
 #pragma unroll
@@ -130,19 +136,20 @@ __global__ __launch_bounds__(kWave * kWavesPerGroup) void combine_kernel(DecodeP
   for (int h = 0; h < G; ++h)
     asm volatile("" ::"v"(la[h]), "v"(lb[h]), "v"(oa[h].x), "v"(oa[h].y), "v"(ob[h].x),
                  "v"(ob[h].y));
-  if (s >= n) return;
-  const int32_t cost = pair_cost(a.nb);
+  if (s >= n >> kShift) return;
+  const int32_t cost = pair_cost(a.nb, kMode);
   if (a.x <= cost) return;                      // no tile of the pair before the boundary
   const int32_t first_tile = a.pos - a.x + cost;
-  const SliceGeom geo = make_slice_geom(W, n, p.xcd8 != 0);
-  const int32_t prev_start = slice_start(s - 1, geo);
+  const Cuts cuts = make_cuts(plan_geom(W, n, p.xcd8 != 0, kMode), kMode, wv);
+  const int32_t prev_start = cuts.first_of(s - 1);
   if (first_tile < prev_start) return;          // an earlier boundary cuts it first
-  const int32_t c1 = slice_of(first_tile + a.nb - 1, geo);
+  const int32_t c1 = cuts.holder(first_tile + a.nb - 1);
+  const int32_t g = kMode == kHeadSlices ? a.g * kHeadsPerSlice + wv : a.g;
   if (c1 == s && first_tile > prev_start) {
-    merge_two_values<G>(p, a.b, a.g, la, lb, oa, ob, lane);  // slots 2s-1, 2s
+    merge_two_values<G>(p, a.b, g, la, lb, oa, ob, lane);
     return;
   }
-  merge_pair<G, false>(p, p.part_o, p.part_lse, 0, a.b, a.g, first_tile, s - 1, c1, geo, lane);
+  merge_pair<G, false>(p, p.part_o, p.part_lse, 0, a.b, g, first_tile, s - 1, c1, cuts, lane);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ dst, size_t words) {
@@ -210,20 +217,33 @@ __global__ __launch_bounds__(256) void validate_kernel(const int32_t* __restrict
 
 hipError_t launch_plan(const int32_t* lens, int32_t batch, int32_t hkv, int32_t mbps,
                        int32_t max_slices, int32_t min_tiles, int32_t quantum, int32_t xcd8,
-                       PlanHeader* hdr, SliceStart* starts, int32_t* prefix, hipStream_t stream) {
+                       SliceMode mode, PlanHeader* hdr, SliceStart* starts, int32_t* prefix, hipStream_t stream) {
   plan_kernel<<<1, kPlanThreads, 0, stream>>>(lens, batch, hkv, mbps, max_slices, min_tiles,
-                                              quantum, xcd8, hdr, starts, prefix);
+                                              quantum, xcd8, mode, hdr, starts, prefix);
   return hipGetLastError();
 }
 
-hipError_t launch_combine(const DecodeParams& p, int32_t group, int32_t grid, hipStream_t stream) {
+namespace {
+
+template <int G>
+void launch_combine_g(const DecodeParams& p, SliceMode mode, int32_t grid, hipStream_t stream) {
   const dim3 block(kWave * kWavesPerGroup);
+  if (mode == kHeadSlices)
+    combine_kernel<G, kHeadSlices><<<grid, block, 0, stream>>>(p);
+  else
+    combine_kernel<G, kWaveSlices><<<grid, block, 0, stream>>>(p);
+}
+
+}  // namespace
+
+hipError_t launch_combine(const DecodeParams& p, int32_t group, SliceMode mode, int32_t grid,
+                          hipStream_t stream) {
   switch (group) {
-    case 1: combine_kernel<1><<<grid, block, 0, stream>>>(p); break;
-    case 2: combine_kernel<2><<<grid, block, 0, stream>>>(p); break;
-    case 4: combine_kernel<4><<<grid, block, 0, stream>>>(p); break;
-    case 8: combine_kernel<8><<<grid, block, 0, stream>>>(p); break;
-    case 16: combine_kernel<16><<<grid, block, 0, stream>>>(p); break;
+    case 1: launch_combine_g<1>(p, mode, grid, stream); break;
+    case 2: launch_combine_g<2>(p, mode, grid, stream); break;
+    case 4: launch_combine_g<4>(p, mode, grid, stream); break;
+    case 8: launch_combine_g<8>(p, mode, grid, stream); break;
+    case 16: launch_combine_g<16>(p, mode, grid, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
