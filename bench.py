@@ -43,8 +43,8 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
 PEAK_PCIE_GBS = 64.0           # PCIe 5.0 x16 host link, one direction (32 GT/s x 16 lanes)
 MALL_BYTES = 256 * 2 ** 20     # Infinity Cache
 METRIC = "decode-attention achieved HBM GB/s (% of peak) + tokens/sec per layer, 1 GPU"
-KERNEL_SOURCES = ("decode_mfma.hip", "decode_valu.hip", "decode_common.h", "decode_stream.h",
-                  "neo_internal.h")
+KERNEL_SOURCES = ("decode_mfma.hip", "decode_valu.hip", "decode_common.h", "decode_pair.h",
+                  "decode_stream.h", "neo_internal.h")
 SEQ_DESC = {1: "U[64,512]", 2: "U[512,2048]", 3: "lognormal(median 1500, sigma 0.6) clip [128,8192]",
             4: "U[256,4096]", 5: "8 x 32768 + 1016 x U[16,256]",
             6: "U[256,4096] (one GPU's share of the 70B layer at 8-way tensor parallelism)"}
@@ -67,8 +67,7 @@ def kernel_source_sha(variant: str) -> str:
     h.update(" ".join(_build.HIPCC_SOURCE_FLAGS.get(f"decode_{variant.split('_')[0]}.hip",
                                                     [])).encode())
     for name in KERNEL_SOURCES:
-        if name.startswith("decode_") and name != "decode_common.h" and \
-                name != f"decode_{variant.split('_')[0]}.hip":
+        if name.endswith(".hip") and name != f"decode_{variant.split('_')[0]}.hip":
             continue
         with open(os.path.join(ROOT, "paper_2411_01142_amd", "csrc", name), "rb") as f:
             h.update(f.read())

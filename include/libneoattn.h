@@ -97,8 +97,8 @@ typedef enum {
 /* How the call is launched (neo_decode_attention_ex). */
 typedef enum {
   NEO_SCHEDULE_AUTO = 0,       /* fused (equal or fastest on MI355X for every length mix tried) */
-  NEO_SCHEDULE_FUSED = 1,      /* one kernel: each wavefront plans its own slice from seq_lens
-                                  and the last slice to finish a split request merges it */
+  NEO_SCHEDULE_FUSED = 1,      /* one kernel: each slice is planned by its own wavefronts from
+                                  seq_lens, the last slice to finish a split request merges it */
   NEO_SCHEDULE_STAGED = 2,     /* three kernels: plan, decode, log-sum-exp combine */
   NEO_SCHEDULE_TWO_KERNEL = 3  /* decode (planning in-wave, recording the plan), then combine */
 } neo_schedule;
@@ -137,11 +137,12 @@ neo_status neo_decode_workspace_init(void* workspace, size_t workspace_bytes, vo
  * The first eleven arguments follow the problem statement in that order; the rest
  * are what a device pointer cannot carry: batch size, block-table row stride
  * (max_blocks_per_seq), pool size (num_blocks), the workspace and the stream.
- * Enqueues one kernel: each wavefront plans its own slice of the batch from
- * seq_lens, streams its tiles, and the last slice to finish a request that
- * was split merges the partial outputs in the same kernel (the staged and
- * two-kernel launches of neo_decode_attention_ex add a plan and a combine
- * kernel). Reads q, k_cache, v_cache, block_table and seq_lens; writes out and
+ * Enqueues one kernel: each wavefront (or workgroup) plans its own slice of the
+ * batch from seq_lens, streams its tiles, and the last slice to finish a
+ * request that was split merges the partial outputs in the same kernel (the
+ * staged and two-kernel launches of neo_decode_attention_ex add a plan and a
+ * combine kernel; a small batch, whose requests are divided without a plan,
+ * is one kernel under every schedule). Reads q, k_cache, v_cache, block_table and seq_lens; writes out and
  * the workspace.
  * Workspace: at least neo_decode_workspace_bytes(batch, num_q_heads,
  * num_kv_heads, head_dim) bytes, 256-byte aligned, zero-filled before its

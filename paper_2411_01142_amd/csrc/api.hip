@@ -188,27 +188,62 @@ neo_status check_decode(const void* q, const void* k_cache, const void* v_cache,
   return NEO_OK;
 }
 
-// Who runs a slice of the plan (SliceMode), from what the host knows: the
-// batch, the heads and the table's width, which bounds the lengths. Head
-// slices need whole groups of four kv heads, and pay once every compute unit
-// has a few (request, four heads) pairs with some blocks to stream: below that
-// a slice is a part of one or two pairs and the cut pairs' partials all cross
-// workgroups, where wave slices merge most of them in LDS. Measured, wave /
-// head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512, 2048]
-// tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512 of
-// U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50, 200]
-// tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52 blocks)
-// 53.9 / 54.0. A caller's slice cap is a cap on wavefronts' slices.
+// How a call is divided (SliceMode, and workgroups of a pair for kPairs), from
+// what the host knows: the batch, the heads and the table's width (mbps), which
+// bounds the lengths. A caller's slice cap is a cap on wavefronts' slices.
+struct Route {
+  neo::SliceMode mode;
+  int32_t parts;
+};
+
+// kPairs: every pair gets the same workgroups whatever its length, so it suits
+// batches whose longest pair cannot keep few workgroups busy long after the
+// others are done. Up to 32 pairs always (one request of 30000 tokens among 31
+// short ones, one kv head: 219 us planned, 24 here), and up to four pairs per
+// compute unit while a workgroup has at most 128 blocks (about 14 us of
+// reading); more pairs than that stream better in slices (2048 pairs of U[50,
+// 200] tokens: 30 us planned, 35 here). A pair of at most 32 blocks is not
+// worth a merge (19 blocks: 6.8 us by one workgroup, 8.3 by two). Workgroups
+// beyond one per compute unit run in rounds, so the second one is given only
+// where a pair then has at least four (96 pairs of up to 500 blocks: 57 us
+// planned, 51 with two workgroups, 45 with five; 256 pairs of up to 250: 57
+// with one, 59 with two).
+constexpr int32_t kPairsAlways = 32;
+constexpr int32_t kPairsPerCu = 4;
+constexpr int32_t kPairBlocksPerPart = 128;
+constexpr int32_t kPairOnePartBlocks = 32;
+
+// Head slices need whole groups of four kv heads, and pay once every compute
+// unit has a few (request, four heads) pairs with some blocks to stream: below
+// that a slice is a part of one or two pairs and the cut pairs' partials all
+// cross workgroups, where wave slices merge most of them in LDS. Measured, wave
+// / head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512,
+// 2048] tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512
+// of U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50,
+// 200] tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52
+// blocks) 53.9 / 54.0.
 constexpr int32_t kHeadPairsPerCu = 2;
 constexpr int32_t kHeadBlocksPerCu = 64;
-neo::SliceMode slice_mode(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv,
-                          int32_t mbps, int32_t cus) {
-  if (variant != NEO_VARIANT_MFMA || max_slices != 0 || hkv % neo::kHeadsPerSlice != 0)
-    return neo::kWaveSlices;
-  const int64_t pairs = (int64_t)batch * (hkv / neo::kHeadsPerSlice);
-  return pairs >= (int64_t)kHeadPairsPerCu * cus && pairs * mbps >= (int64_t)kHeadBlocksPerCu * cus
-             ? neo::kHeadSlices
-             : neo::kWaveSlices;
+
+Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int32_t mbps,
+            int32_t cus) {
+  if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {neo::kWaveSlices, 0};
+  const int64_t pairs = (int64_t)batch * hkv;
+  if (pairs <= (int64_t)kPairsPerCu * cus) {
+    const int32_t chunks = (mbps - 1) / neo::kPairChunk + 1;
+    const int32_t n = (int32_t)pairs, c = std::min(cus, NEO_MAX_SLICES / 8);
+    int32_t parts = mbps <= kPairOnePartBlocks ? 1 : std::max(1, std::min(c / n, chunks));
+    if (mbps / kPairBlocksPerPart >= parts && n <= c / 2) parts = std::min(2 * c / n, chunks);
+    if (n <= kPairsAlways || mbps <= (int64_t)kPairBlocksPerPart * parts)
+      return {neo::kPairs, parts};
+  }
+  if (hkv % neo::kHeadsPerSlice == 0) {
+    const int64_t groups = pairs / neo::kHeadsPerSlice;
+    if (groups >= (int64_t)kHeadPairsPerCu * cus &&
+        groups * mbps >= (int64_t)kHeadBlocksPerCu * cus)
+      return {neo::kHeadSlices, 0};
+  }
+  return {neo::kWaveSlices, 0};
 }
 
 // ----------------------------------------------------------------- static scratch
@@ -221,7 +256,10 @@ neo::SliceMode slice_mode(int32_t variant, int32_t max_slices, int32_t batch, in
 // plan of that entry point uses at most kScratchSlices slices (one per wave
 // of one 4-wave workgroup per CU on a 256-CU part). Every GPU the library
 // runs on holds one copy until the process ends (16.1 MiB).
+// A plan without slices (kPairs) uses a counter per pair and a partial slot per
+// workgroup of a pair, at most 2 NEO_MAX_SLICES / 8 of each.
 constexpr int32_t kScratchSlices = 1024;
+static_assert(2 * (NEO_MAX_SLICES / 8) <= kScratchSlices, "kPairs must fit the scratch");
 constexpr int32_t kScratchMaxGroup = 16;
 constexpr size_t kScratchCountersOff = 0;
 constexpr size_t kScratchLseOff =
@@ -325,7 +363,7 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
                               : schedule == NEO_SCHEDULE_STAGED   ? neo::kStaged
                                                                   : neo::kFused;
 
-  const neo::SliceMode mode = slice_mode(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq, cus);
+  const Route r = route(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq, cus);
 
   char* ws = static_cast<char*>(workspace);
   neo::DecodeParams p;
@@ -349,14 +387,16 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
   p.min_tiles = min_tiles;
   p.slice_quantum = quantum;
   p.xcd8 = xcds == 8;
+  p.parts = r.parts;
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (sched == neo::kStaged) {
+  // A call without slices has nothing to plan or combine.
+  if (sched == neo::kStaged && r.mode != neo::kPairs) {
     e = neo::launch_plan(seq_lens, batch, num_kv_heads, max_blocks_per_seq, slices, min_tiles,
-                         quantum, p.xcd8, mode, reinterpret_cast<neo::PlanHeader*>(ws + wl.hdr),
+                         quantum, p.xcd8, r.mode, reinterpret_cast<neo::PlanHeader*>(ws + wl.hdr),
                          reinterpret_cast<neo::SliceStart*>(ws + wl.starts),
                          reinterpret_cast<int32_t*>(ws + wl.prefix), s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "plan launch: %s", hipGetErrorString(e));
@@ -367,14 +407,14 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "event record: %s", hipGetErrorString(e));
   }
   e = variant == NEO_VARIANT_VALU ? neo::launch_decode_valu(p, group, sched, grid, s)
-                                  : neo::launch_decode_mfma(p, group, mode, sched, grid, s);
+                                  : neo::launch_decode_mfma(p, group, r.mode, sched, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   if (decode_end_event) {
     e = hipEventRecord(static_cast<hipEvent_t>(decode_end_event), s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "event record: %s", hipGetErrorString(e));
   }
-  if (sched != neo::kFused) {
-    e = neo::launch_combine(p, group, mode, grid, s);
+  if (sched != neo::kFused && r.mode != neo::kPairs) {
+    e = neo::launch_combine(p, group, r.mode, grid, s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "combine launch: %s", hipGetErrorString(e));
   }
   return ok();
@@ -460,8 +500,9 @@ neo_status neo_decode_attention_noalloc(const void* q, const void* k_cache, cons
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
   const int32_t grid = (slices + neo::kWavesPerGroup - 1) / neo::kWavesPerGroup;
-  const hipError_t e = neo::launch_decode_mfma(
-      p, group, slice_mode(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus), neo::kFused, grid, s);
+  const Route r = route(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus);
+  p.parts = r.parts;
+  const hipError_t e = neo::launch_decode_mfma(p, group, r.mode, neo::kFused, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   return ok();
 }

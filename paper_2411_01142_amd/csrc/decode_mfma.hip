@@ -21,6 +21,7 @@
 // each lane keeps a partial sum of its own tokens' weights. The weights enter
 // the second product as bf16 hi + lo halves (two products), which keeps ~16
 // mantissa bits of each weight.
+#include "decode_pair.h"
 #include "decode_stream.h"
 
 namespace neo {
@@ -271,6 +272,18 @@ __global__ __launch_bounds__(kWave * kWavesPerGroup, kMode == kHeadSlices ? 1 : 
   }
 }
 
+// The first three arguments (five dwords) address the first reads and arrive
+// preloaded; see above.
+template <int G>
+__global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_pair_kernel(
+    const int32_t* __restrict__ lens, const int32_t* __restrict__ table, int32_t mbps,
+    DecodeParams p) {
+  p.lens = lens;
+  p.table = table;
+  p.mbps = mbps;
+  pair_driver<MfmaFamily<G>, G>(p);
+}
+
 template <int G, SliceMode kMode>
 hipError_t launch_g(const DecodeParams& p, Schedule sched, int32_t grid, hipStream_t stream) {
   const dim3 block(kWave * kWavesPerGroup);
@@ -291,6 +304,11 @@ hipError_t launch_g(const DecodeParams& p, Schedule sched, int32_t grid, hipStre
 template <int G>
 hipError_t launch_mode(const DecodeParams& p, SliceMode mode, Schedule sched, int32_t grid,
                        hipStream_t stream) {
+  if (mode == kPairs) {
+    decode_pair_kernel<G><<<dim3(p.parts, p.hkv, p.batch), kWave * kPairWaves, 0, stream>>>(
+        p.lens, p.table, p.mbps, p);
+    return hipGetLastError();
+  }
   return mode == kHeadSlices ? launch_g<G, kHeadSlices>(p, sched, grid, stream)
                              : launch_g<G, kWaveSlices>(p, sched, grid, stream);
 }

@@ -43,7 +43,13 @@ constexpr int32_t kLongPairBlocks = 32;
 //  kWaveSlices: a pair is (request, kv head); one slice per wavefront.
 //  kHeadSlices: a pair is (request, four kv heads); one slice per workgroup,
 //    whose four wavefronts walk the same blocks together, one head each.
-enum SliceMode { kWaveSlices = 0, kHeadSlices = 1 };
+//  kPairs: no line and no slices; every (request, kv head) pair has the same
+//    number of workgroups (DecodeParams::parts), which take its chunks of
+//    kPairChunk blocks in turn.
+enum SliceMode { kWaveSlices = 0, kHeadSlices = 1, kPairs = 2 };
+constexpr int kPairWaves = 8;         // kPairs: wavefronts of a workgroup
+constexpr int kPairTilesPerWave = 2;  // of a chunk
+constexpr int kPairChunk = kPairWaves * kPairTilesPerWave;
 constexpr int kHeadsPerSlice = 4;  // kHeadSlices: kv heads of a pair, one per wavefront
 // Head slices stream across pair ends, which costs a pair little more than its
 // arithmetic.
@@ -229,6 +235,7 @@ struct DecodeParams {
   int32_t max_slices, min_tiles;  // min_tiles == 0: the default slice policy
   int32_t slice_quantum;          // compute units x wavefronts per workgroup
   int32_t xcd8;                   // the device has eight XCDs (slice weights)
+  int32_t parts;              // kPairs: workgroups of a pair
   float scale_log2;           // scale * log2(e)
   int64_t blk_stride;         // elements from one block of a cache to the next (K and V alike)
 };
