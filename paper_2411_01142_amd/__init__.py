@@ -24,6 +24,7 @@ heads in groups. Layouts (torch tensors, all on one GPU):
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 import threading
@@ -50,6 +51,13 @@ STATUS = {0: "NEO_OK", 1: "NEO_ERR_INVALID_ARG", 2: "NEO_ERR_UNSUPPORTED",
 _lib = None
 _lock = threading.Lock()
 _workspaces = {}
+
+# A decode call's kernel can be shorter than the Python around it (8 us against
+# 17 us for one request of 877 tokens), so the two calls of a decoding loop,
+# decode_attention and kv_append, check their tensors in one pass over plain
+# attributes, read the current stream and device as integers and enter a device
+# context only to change the device. Anything the pass does not accept goes
+# through the full checks, which raise or accept it.
 
 
 class NeoError(RuntimeError):
@@ -190,6 +198,58 @@ def _require_cache(t, name, ndim, *, pinned_ok=False):
     return int(t.stride(0))
 
 
+def _is_plain(torch, t, device):
+    """Whether t is an ordinary contiguous bf16 tensor of three dims on ``device``."""
+    return (type(t) is torch.Tensor and t.device == device and t.dtype is torch.bfloat16
+            and t.dim() == 3 and t.is_contiguous())
+
+
+def _paged_stride(torch, device, k, v, table, lens):
+    """The caches' block stride in elements if k, v, table and lens are what
+    ``_shared_stride`` and ``_require`` accept, on the GPU ``device``; None when
+    this pass cannot say so."""
+    T, bf16, i32 = torch.Tensor, torch.bfloat16, torch.int32
+    if not (type(k) is T and type(v) is T and type(table) is T and type(lens) is T
+            and k.is_cuda and k.device == device and v.device == device
+            and table.device == device and lens.device == device
+            and k.dtype is bf16 and v.dtype is bf16 and table.dtype is i32 and lens.dtype is i32
+            and k.dim() == 5 and v.dim() == 4 and table.dim() == 2 and lens.dim() == 1
+            and table.is_contiguous() and lens.is_contiguous()):
+        return None
+    _, _, a, b, c = k.shape
+    _, heads, d, e = v.shape
+    ks, *k_inner = k.stride()
+    vs, *v_inner = v.stride()
+    if (ks != vs or ks % 8 != 0 or k_inner != [a * b * c, b * c, c, 1] or v_inner != [d * e, e, 1]
+            or ks < k.shape[1] * a * b * c or vs < heads * d * e):
+        return None
+    return ks
+
+
+@functools.lru_cache(maxsize=256)
+def _cached_workspace_bytes(batch, num_q_heads, num_kv_heads, head_dim):
+    return workspace_bytes(batch, num_q_heads, num_kv_heads, head_dim)
+
+
+def _raw_stream(torch, stream, device):
+    """Handle (an integer) of ``stream``, or of torch's current stream on ``device``."""
+    if stream is not None:
+        return stream.cuda_stream
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if get is not None and device.index is not None:
+        return get(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+def _on_device(torch, device, fn, args):
+    """fn(*args) with ``device`` current."""
+    get = getattr(torch._C, "_cuda_getDevice", None)
+    if get is not None and get() == device.index:
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
+
+
 def new_kv_cache(num_blocks: int, num_kv_heads: int, device="cuda", head_dim: int = 128,
                  block_size: int = 16):
     """(k_cache, v_cache) views of one allocation ``[num_blocks][K, V][num_kv_heads][tile]``:
@@ -264,23 +324,26 @@ def decode_attention(q, k_cache, v_cache, block_table, seq_lens, scale=None, out
     ``stream`` (default: torch's current stream) without synchronising.
     """
     torch = _torch()
-    lib = load_library()
-    _require(q, "q", torch.bfloat16, 3)
-    k_stride = _shared_stride(k_cache, "k_cache", v_cache, "v_cache")
-    _require(block_table, "block_table", torch.int32, 2)
-    _require(seq_lens, "seq_lens", torch.int32, 1)
+    lib = _lib or load_library()
+    device = q.device if isinstance(q, torch.Tensor) else None
+    k_stride = _paged_stride(torch, device, k_cache, v_cache, block_table, seq_lens)
+    if (k_stride is None or type(q) is not torch.Tensor or q.dtype is not torch.bfloat16
+            or q.dim() != 3 or not q.is_contiguous()):
+        _require(q, "q", torch.bfloat16, 3)
+        k_stride = _shared_stride(k_cache, "k_cache", v_cache, "v_cache")
+        _require(block_table, "block_table", torch.int32, 2)
+        _require(seq_lens, "seq_lens", torch.int32, 1)
     B, Hq, D = q.shape
     NB, Hkv, npieces, bs, x = k_cache.shape
     if npieces * x != D or x != 8:
         raise ValueError(f"k_cache shape {tuple(k_cache.shape)} does not match head_dim {D}")
-    if tuple(v_cache.shape) != (NB, Hkv, D, bs):
+    if v_cache.shape != (NB, Hkv, D, bs):
         raise ValueError(f"v_cache shape {tuple(v_cache.shape)} != {(NB, Hkv, D, bs)}")
     if block_table.shape[0] != B or seq_lens.shape[0] != B:
         raise ValueError("block_table and seq_lens must have batch rows")
-    devs = {t.device for t in (q, k_cache, v_cache, block_table, seq_lens)}
-    if len(devs) != 1:
+    if not (k_cache.device == device and v_cache.device == device
+            and block_table.device == device and seq_lens.device == device):
         raise ValueError("all tensors must be on one device")
-    device = q.device
     if scale is None:
         scale = 1.0 / math.sqrt(D)
     if out is None:
@@ -293,21 +356,21 @@ def decode_attention(q, k_cache, v_cache, block_table, seq_lens, scale=None, out
         raise ValueError(f"variant must be one of {sorted(VARIANTS)}")
     if schedule not in SCHEDULES:
         raise ValueError(f"schedule must be one of {sorted(SCHEDULES)}")
-    st = _stream_of(stream, device)
-    sh = ctypes.c_void_p(st.cuda_stream)
+    sh = _raw_stream(torch, stream, device)
     if B == 0:
         return out
-    need = workspace_bytes(B, Hq, Hkv, D)
+    need = _cached_workspace_bytes(B, Hq, Hkv, D)
     if workspace is None:
-        workspace = _workspace(need, device, st)
+        workspace = _workspaces.get((device.index, sh))
+        if workspace is None or workspace.numel() < need:
+            workspace = _workspace(need, device, _stream_of(stream, device))
     else:
         _require(workspace, "workspace", torch.uint8, 1)
-    with torch.cuda.device(device):
-        _check(lib.neo_decode_attention_ex(
-            q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
+    args = (q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
             seq_lens.data_ptr(), Hq, Hkv, D, bs, float(scale), out.data_ptr(), B,
             block_table.shape[1], NB, workspace.data_ptr(), workspace.numel(),
-            VARIANTS[variant], SCHEDULES[schedule], int(max_slices), k_stride, sh))
+            VARIANTS[variant], SCHEDULES[schedule], int(max_slices), k_stride, sh)
+    _check(_on_device(torch, device, lib.neo_decode_attention_ex, args))
     return out
 
 
@@ -366,22 +429,23 @@ def kv_append(k_cache, v_cache, k_new, v_new, block_table, seq_lens, *, stream=N
     paged caches at token seq_lens[b] - 1 (in place, on ``stream``). The caches may
     be dense or share one block stride (``new_kv_cache``)."""
     torch = _torch()
-    lib = load_library()
-    stride = _shared_stride(k_cache, "k_cache", v_cache, "v_cache")
-    _require(k_new, "k_new", torch.bfloat16, 3)
-    _require(v_new, "v_new", torch.bfloat16, 3)
-    _require(block_table, "block_table", torch.int32, 2)
-    _require(seq_lens, "seq_lens", torch.int32, 1)
+    lib = _lib or load_library()
+    device = k_cache.device if isinstance(k_cache, torch.Tensor) else None
+    stride = _paged_stride(torch, device, k_cache, v_cache, block_table, seq_lens)
+    if stride is None or not (_is_plain(torch, k_new, device) and _is_plain(torch, v_new, device)):
+        stride = _shared_stride(k_cache, "k_cache", v_cache, "v_cache")
+        _require(k_new, "k_new", torch.bfloat16, 3)
+        _require(v_new, "v_new", torch.bfloat16, 3)
+        _require(block_table, "block_table", torch.int32, 2)
+        _require(seq_lens, "seq_lens", torch.int32, 1)
     NB, Hkv, npieces, bs, x = k_cache.shape
     B = seq_lens.shape[0]
-    if tuple(k_new.shape) != (B, Hkv, npieces * x) or k_new.shape != v_new.shape:
+    if k_new.shape != (B, Hkv, npieces * x) or k_new.shape != v_new.shape:
         raise ValueError("k_new and v_new must be [batch, num_kv_heads, head_dim]")
-    sh = _stream_handle(stream, k_cache.device)
-    with torch.cuda.device(k_cache.device):
-        _check(lib.neo_kv_append(k_cache.data_ptr(), v_cache.data_ptr(), k_new.data_ptr(),
-                                 v_new.data_ptr(), block_table.data_ptr(), seq_lens.data_ptr(),
-                                 B, block_table.shape[1], Hkv, npieces * x, bs, NB, stride,
-                                 sh))
+    args = (k_cache.data_ptr(), v_cache.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+            block_table.data_ptr(), seq_lens.data_ptr(), B, block_table.shape[1], Hkv,
+            npieces * x, bs, NB, stride, _raw_stream(torch, stream, device))
+    _check(_on_device(torch, device, lib.neo_kv_append, args))
 
 
 def _shared_stride(k, k_name, v, v_name, *, pinned_ok=False):
