@@ -188,12 +188,13 @@ neo_status check_decode(const void* q, const void* k_cache, const void* v_cache,
   return NEO_OK;
 }
 
-// How a call is divided (SliceMode, and workgroups of a pair for kPairs), from
-// what the host knows: the batch, the heads and the table's width (mbps), which
-// bounds the lengths. A caller's slice cap is a cap on wavefronts' slices.
+// How a call is divided (SliceMode, and for kPairs the workgroups of a pair and
+// the order of the requests), from what the host knows: the batch, the heads
+// and the table's width (mbps), which bounds the lengths. A caller's slice cap
+// is a cap on wavefronts' slices.
 struct Route {
   neo::SliceMode mode;
-  int32_t parts;
+  int32_t parts, longest_first;
 };
 
 // kPairs: every pair gets the same workgroups whatever its length, so it suits
@@ -201,9 +202,13 @@ struct Route {
 // others are done. Up to 32 pairs always (one request of 30000 tokens among 31
 // short ones, one kv head: 219 us planned, 24 here), and up to four pairs per
 // compute unit while a workgroup has at most 128 blocks (about 14 us of
-// reading); more pairs than that stream better in slices (2048 pairs of U[50,
-// 200] tokens: 30 us planned, 35 here). A pair of at most 32 blocks is not
-// worth a merge (19 blocks: 6.8 us by one workgroup, 8.3 by two). Workgroups
+// reading), or 256 where the pairs run in rounds, longest first (512 pairs of
+// U[256, 4096] tokens: 106 us planned, 95 here; 256 pairs in one round,
+// lognormal around 1000 and up to 4000: 37.5 planned, 40.7 here); more pairs
+// than that stream better in slices (2048 pairs of U[50, 200] tokens: 30 us
+// planned, 35 here). A pair of at most 32 blocks is not worth a merge (19
+// blocks: 6.8 us by one workgroup, 8.3 by two) or an order (64 requests of
+// U[50, 150] tokens: 9.7 in index order, 11.7 longest first). Workgroups
 // beyond one per compute unit run in rounds, so the second one is given only
 // where a pair then has at least four (96 pairs of up to 500 blocks: 57 us
 // planned, 51 with two workgroups, 45 with five; 256 pairs of up to 250: 57
@@ -211,7 +216,8 @@ struct Route {
 constexpr int32_t kPairsAlways = 32;
 constexpr int32_t kPairsPerCu = 4;
 constexpr int32_t kPairBlocksPerPart = 128;
-constexpr int32_t kPairOnePartBlocks = 32;
+constexpr int32_t kPairBlocksOrdered = 256;
+constexpr int32_t kPairShortBlocks = 32;
 
 // Head slices need whole groups of four kv heads, and pay once every compute
 // unit has a few (request, four heads) pairs with some blocks to stream: below
@@ -227,23 +233,25 @@ constexpr int32_t kHeadBlocksPerCu = 64;
 
 Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int32_t mbps,
             int32_t cus) {
-  if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {neo::kWaveSlices, 0};
+  if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {neo::kWaveSlices, 0, 0};
   const int64_t pairs = (int64_t)batch * hkv;
   if (pairs <= (int64_t)kPairsPerCu * cus) {
     const int32_t chunks = (mbps - 1) / neo::kPairChunk + 1;
     const int32_t n = (int32_t)pairs, c = std::min(cus, NEO_MAX_SLICES / 8);
-    int32_t parts = mbps <= kPairOnePartBlocks ? 1 : std::max(1, std::min(c / n, chunks));
+    int32_t parts = mbps <= kPairShortBlocks ? 1 : std::max(1, std::min(c / n, chunks));
     if (mbps / kPairBlocksPerPart >= parts && n <= c / 2) parts = std::min(2 * c / n, chunks);
-    if (n <= kPairsAlways || mbps <= (int64_t)kPairBlocksPerPart * parts)
-      return {neo::kPairs, parts};
+    const bool ordered = n > cus && mbps > kPairShortBlocks && batch <= neo::kMaxOrderedBatch;
+    if (n <= kPairsAlways || mbps <= (int64_t)kPairBlocksPerPart * parts ||
+        (ordered && mbps <= kPairBlocksOrdered))
+      return {neo::kPairs, parts, ordered};
   }
   if (hkv % neo::kHeadsPerSlice == 0) {
     const int64_t groups = pairs / neo::kHeadsPerSlice;
     if (groups >= (int64_t)kHeadPairsPerCu * cus &&
         groups * mbps >= (int64_t)kHeadBlocksPerCu * cus)
-      return {neo::kHeadSlices, 0};
+      return {neo::kHeadSlices, 0, 0};
   }
-  return {neo::kWaveSlices, 0};
+  return {neo::kWaveSlices, 0, 0};
 }
 
 // ----------------------------------------------------------------- static scratch
@@ -388,6 +396,7 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
   p.slice_quantum = quantum;
   p.xcd8 = xcds == 8;
   p.parts = r.parts;
+  p.longest_first = r.longest_first;
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
 
@@ -502,6 +511,7 @@ neo_status neo_decode_attention_noalloc(const void* q, const void* k_cache, cons
   const int32_t grid = (slices + neo::kWavesPerGroup - 1) / neo::kWavesPerGroup;
   const Route r = route(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus);
   p.parts = r.parts;
+  p.longest_first = r.longest_first;
   const hipError_t e = neo::launch_decode_mfma(p, group, r.mode, neo::kFused, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   return ok();

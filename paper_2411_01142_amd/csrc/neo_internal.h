@@ -50,6 +50,7 @@ enum SliceMode { kWaveSlices = 0, kHeadSlices = 1, kPairs = 2 };
 constexpr int kPairWaves = 8;         // kPairs: wavefronts of a workgroup
 constexpr int kPairTilesPerWave = 2;  // of a chunk
 constexpr int kPairChunk = kPairWaves * kPairTilesPerWave;
+constexpr int kMaxOrderedBatch = 1024;
 constexpr int kHeadsPerSlice = 4;  // kHeadSlices: kv heads of a pair, one per wavefront
 // Head slices stream across pair ends, which costs a pair little more than its
 // arithmetic.
@@ -236,6 +237,7 @@ struct DecodeParams {
   int32_t slice_quantum;          // compute units x wavefronts per workgroup
   int32_t xcd8;                   // the device has eight XCDs (slice weights)
   int32_t parts;              // kPairs: workgroups of a pair
+  int32_t longest_first;      // kPairs: order of the requests (batch <= kMaxOrderedBatch)
   float scale_log2;           // scale * log2(e)
   int64_t blk_stride;         // elements from one block of a cache to the next (K and V alike)
 };

@@ -2,7 +2,7 @@
 head) pair goes to one workgroup or to a fixed number of them. At the edges of
 that division (no tokens, one tile, chunks of 16 blocks and their remainders,
 fewer chunks than workgroups, more chunks than workgroups, lengths far below
-the table's width), for every query group, against the oracle, across launch
+the table's width, batches whose requests are taken longest first), for every query group, against the oracle, across launch
 schedules and entry points, and call after call on one workspace."""
 import ctypes
 
@@ -42,6 +42,11 @@ CASES = {
     "one_long_many_short": (1, [30000] + [200] * 20 + [0, 1], 0),
     "wide_table": (8, [100, 900, 1, 300], 700),
     "most_pairs": (8, [1, 700, 333, 0] * 16 + [2048] * 64, 0),
+    # more pairs than compute units: longest first
+    "ordered": (4, [16 * (i * 37 % 200) + i % 17 for i in range(100)], 0),
+    "ordered_equal": (8, [530] * 33, 0),
+    "ordered_one_long": (2, [90] * 150 + [4000] + [0] * 20, 0),
+    "ordered_many_groups": (1, [(i * 7919) % 1000 for i in range(1000)], 1),
 }
 
 
