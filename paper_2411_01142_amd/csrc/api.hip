@@ -204,9 +204,11 @@ struct Route {
 // compute unit while a workgroup has at most 128 blocks (about 14 us of
 // reading), or 256 where the pairs run in rounds, longest first (512 pairs of
 // U[256, 4096] tokens: 106 us planned, 95 here; 256 pairs in one round,
-// lognormal around 1000 and up to 4000: 37.5 planned, 40.7 here); more pairs
-// than that stream better in slices (2048 pairs of U[50, 200] tokens: 30 us
-// planned, 35 here). A pair of at most 32 blocks is not worth a merge (19
+// lognormal around 1000 and up to 4000: 37.5 planned, 40.7 here). Up to eight
+// pairs per compute unit if they have room to be long enough for a workgroup's
+// start (2048 pairs of U[512, 2048] tokens 210 planned, 201 here; of U[50, 200]
+// 30 and 35; 2000 of U[100, 1000] 103 and 112); more pairs stream better in
+// slices (4096 of U[256, 4096]: 681 and 696). A pair of at most 32 blocks is not worth a merge (19
 // blocks: 6.8 us by one workgroup, 8.3 by two) or an order (64 requests of
 // U[50, 150] tokens: 9.7 in index order, 11.7 longest first). Workgroups
 // beyond one per compute unit run in rounds, so the second one is given only
@@ -215,6 +217,8 @@ struct Route {
 // with one, 59 with two).
 constexpr int32_t kPairsAlways = 32;
 constexpr int32_t kPairsPerCu = 4;
+constexpr int32_t kLongPairsPerCu = 8;
+constexpr int32_t kLongPairBlocksMin = 128;
 constexpr int32_t kPairBlocksPerPart = 128;
 constexpr int32_t kPairBlocksOrdered = 256;
 constexpr int32_t kPairShortBlocks = 32;
@@ -235,14 +239,15 @@ Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int
             int32_t cus) {
   if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {neo::kWaveSlices, 0, 0};
   const int64_t pairs = (int64_t)batch * hkv;
-  if (pairs <= (int64_t)kPairsPerCu * cus) {
+  if (pairs <= (int64_t)kPairsPerCu * cus ||
+      (pairs <= (int64_t)kLongPairsPerCu * cus && mbps >= kLongPairBlocksMin)) {
     const int32_t chunks = (mbps - 1) / neo::kPairChunk + 1;
     const int32_t n = (int32_t)pairs, c = std::min(cus, NEO_MAX_SLICES / 8);
     int32_t parts = mbps <= kPairShortBlocks ? 1 : std::max(1, std::min(c / n, chunks));
     if (mbps / kPairBlocksPerPart >= parts && n <= c / 2) parts = std::min(2 * c / n, chunks);
     const bool ordered = n > cus && mbps > kPairShortBlocks && batch <= neo::kMaxOrderedBatch;
-    if (n <= kPairsAlways || mbps <= (int64_t)kPairBlocksPerPart * parts ||
-        (ordered && mbps <= kPairBlocksOrdered))
+    if (n <= kPairsAlways || (ordered && mbps <= kPairBlocksOrdered) ||
+        (n <= kPairsPerCu * cus && mbps <= (int64_t)kPairBlocksPerPart * parts))
       return {neo::kPairs, parts, ordered};
   }
   if (hkv % neo::kHeadsPerSlice == 0) {

@@ -46,6 +46,7 @@ CASES = {
     "ordered": (4, [16 * (i * 37 % 200) + i % 17 for i in range(100)], 0),
     "ordered_equal": (8, [530] * 33, 0),
     "ordered_one_long": (2, [90] * 150 + [4000] + [0] * 20, 0),
+    "ordered_rounds": (8, [(i * 353) % 2049 for i in range(180)], 0),
     "ordered_many_groups": (1, [(i * 7919) % 1000 for i in range(1000)], 1),
 }
 
