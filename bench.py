@@ -860,7 +860,7 @@ def main(argv=None):
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": f"decode_{resolved}_kernel<{case.group}, {schedule}>",
+            "kernel": f"decode {resolved}, group {case.group}, {schedule}",
             "achieved": round(achieved, 2),
             "peak": PEAK_HBM_GBS,
             "unit": "GB/s",
