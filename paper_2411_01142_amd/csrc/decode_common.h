@@ -28,6 +28,17 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr float kLn2 = 0.6931471805599453f;
+// Where a running maximum of scores starts: the lowest finite value, so that it
+// is finite whatever the scores are. Scores of minus infinity then weigh
+// nothing, also where a state or a merge sees no other ones at first (from
+// minus infinity, their difference to the maximum is NaN). A share of nothing
+// but such scores has a denominator of zero: its partial is zero rows with a
+// log-sum-exp of minus infinity, and a pair of nothing else is NaN.
+constexpr float kLowest = -__FLT_MAX__;
+// 1 / denominator of a share; a partial without weight counts as zero rows.
+__device__ inline float share_inverse(float denominator, bool partial) {
+  return partial && denominator == 0.f ? 0.f : 1.f / denominator;
+}
 
 // ----------------------------------------------------------------- tile loads
 
@@ -479,7 +490,7 @@ __device__ inline void merge_pair_heads(const DecodeParams& p, const float* part
   float m[GH], z[GH], a0[GH], a1[GH];
 #pragma unroll
   for (int h = 0; h < GH; ++h) {
-    m[h] = -INFINITY;
+    m[h] = kLowest;
     z[h] = a0[h] = a1[h] = 0.f;
   }
   for (int base = 0; base < k; base += kWave) {

@@ -58,7 +58,7 @@ struct MfmaFamily {
   __device__ static void init(State& st) {
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) st.acc[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    st.m = -INFINITY;
+    st.m = kLowest;
     st.l = 0.f;
   }
 
@@ -100,7 +100,7 @@ struct MfmaFamily {
     }
     float mt = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
     mt = max_over_rows(mt);
-    const float mn = fmaxf(st.m, mt);  // finite: every tile has a valid token
+    const float mn = fmaxf(st.m, mt);  // finite
     const float alpha = __builtin_amdgcn_exp2f(st.m - mn);
     float pr[4];
 #pragma unroll
@@ -131,7 +131,7 @@ struct MfmaFamily {
                                float* __restrict__ lse, int lane) {
     const int col = lane & 15, rq = lane >> 4;
     const float lt = sum_over_rows(st.l);
-    const float inv = 1.f / lt;
+    const float inv = share_inverse(lt, lse != nullptr);
     if (col < G) {
       float* r = rows + col * kHeadDim + 4 * rq;
 #pragma unroll
@@ -160,7 +160,7 @@ struct MfmaFamily {
                                      float* __restrict__ out_rows, int lane) {
     const int col = lane & 15, rq = lane >> 4;
     const float lt = sum_over_rows(st.l);
-    const float inv = 1.f / lt;
+    const float inv = share_inverse(lt, true);
     if (col < G) {
       // Rounded exactly as the stored log-sum-exp of write(): the empty asm
       // makes la an opaque value, so the compiler cannot fuse its multiply
@@ -192,11 +192,11 @@ struct MfmaFamily {
     }
   }
 
-  // The state normalised to output rows; returns each head's natural-log
-  // log-sum-exp (in the lanes of its column).
-  __device__ static float normalise(State& st) {
+  // The state normalised to output rows (partial: a share of them); returns
+  // each head's natural-log log-sum-exp (in the lanes of its column).
+  __device__ static float normalise(State& st, bool partial) {
     const float lt = sum_over_rows(st.l);
-    const float inv = 1.f / lt;
+    const float inv = share_inverse(lt, partial);
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) st.acc[mb] *= inv;
     return (st.m + __log2f(lt)) * kLn2;

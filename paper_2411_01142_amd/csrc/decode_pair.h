@@ -36,7 +36,7 @@ template <int G>
 __device__ inline float2 merge_parts(const DecodeParams& p, int32_t slot0, int32_t k, int h,
                                      int lane) {
   constexpr int kBatch = 16;
-  float m = -INFINITY, z = 0.f, x = 0.f, y = 0.f;
+  float m = kLowest, z = 0.f, x = 0.f, y = 0.f;
   for (int32_t base = 0; base < k; base += kWave) {
     const int32_t cnt = min(kWave, k - base);
     const float got = load_coherent(p.part_lse + (slot0 + base + min(lane, cnt - 1)) * G + h);
@@ -206,7 +206,7 @@ __device__ inline void pair_driver(const DecodeParams& p) {
   const int32_t pair = b * p.hkv + g;
   const int32_t slot = pair * parts + s;
   for (int h = wv; h < G; h += kPairWaves) {
-    float m = -INFINITY, l = 0.f, x = 0.f, y = 0.f;
+    float m = kLowest, l = 0.f, x = 0.f, y = 0.f;
     for (int w = 0; w < shares; ++w) m = fmaxf(m, ms[w][h]);
     for (int w = 0; w < shares; ++w) {
       const float e = __builtin_amdgcn_exp2f(ms[w][h] - m);
@@ -216,7 +216,7 @@ __device__ inline void pair_driver(const DecodeParams& p) {
       x = fmaf(e, v.x, x);
       y = fmaf(e, v.y, y);
     }
-    const float inv = 1.f / l;
+    const float inv = share_inverse(l, k > 1);
     if (k == 1) {
       *reinterpret_cast<float2*>(out + h * kHeadDim + 2 * lane) = float2{x * inv, y * inv};
     } else {

@@ -266,8 +266,9 @@ __device__ inline void stream_driver(const DecodeParams& p) {
   auto finish_segment = [&]() {
     const int32_t kvh = kv_head(g);
     const int32_t row = b * p.hq + kvh * G;
-    const float lse = F::normalise(st);
-    if (j == 0 && jend == nb) {
+    const bool whole = j == 0 && jend == nb;
+    const float lse = F::normalise(st, !whole);
+    if (whole) {
       put_result(row);
       return;
     }

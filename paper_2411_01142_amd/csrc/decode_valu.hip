@@ -72,7 +72,7 @@ struct ValuFamily {
   __device__ static void init(State& st) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      st.m[h] = -INFINITY;
+      st.m[h] = kLowest;
       st.l[h] = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) st.acc[i][h] = 0.f;
@@ -164,7 +164,7 @@ struct ValuFamily {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       const float lt = sum_over_rows(st.l[h]);
-      const float inv = 1.f / lt;
+      const float inv = share_inverse(lt, lse != nullptr);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float a =
