@@ -44,7 +44,7 @@ PEAK_PCIE_GBS = 64.0           # PCIe 5.0 x16 host link, one direction (32 GT/s 
 MALL_BYTES = 256 * 2 ** 20     # Infinity Cache
 METRIC = "decode-attention achieved HBM GB/s (% of peak) + tokens/sec per layer, 1 GPU"
 KERNEL_SOURCES = ("decode_mfma.hip", "decode_valu.hip", "decode_common.h", "decode_pair.h",
-                  "decode_stream.h", "neo_internal.h")
+                  "decode_stream.h", "neo_internal.h", "route.h")
 SEQ_DESC = {1: "U[64,512]", 2: "U[512,2048]", 3: "lognormal(median 1500, sigma 0.6) clip [128,8192]",
             4: "U[256,4096]", 5: "8 x 32768 + 1016 x U[16,256]",
             6: "U[256,4096] (one GPU's share of the 70B layer at 8-way tensor parallelism)"}

@@ -472,6 +472,25 @@ neo_status neo_debug_validate(const int32_t* block_table, const int32_t* seq_len
                               int32_t max_blocks_per_seq, int32_t block_size, int32_t num_blocks,
                               int32_t* error_count, void* stream);
 
+/* How neo_decode_attention divides a call (neo_debug_division). */
+typedef enum {
+  NEO_DIVISION_WAVE_SLICES = 0,  /* planned slices, one per wavefront */
+  NEO_DIVISION_HEAD_SLICES = 1,  /* planned slices, one per workgroup, over four kv heads */
+  NEO_DIVISION_PAIRS = 2,        /* the same workgroups for every (request, kv head) pair */
+  NEO_DIVISION_UNITS = 3,        /* pairs cut into units of one size, chosen from the lengths */
+  NEO_DIVISION_WHOLE = 4         /* one workgroup per pair, longest first */
+} neo_division;
+
+/*
+ * The division (neo_division, in *division) that a decode call of these shapes
+ * takes on a device of `compute_units` compute units. Host only. With head
+ * slices, units and whole pairs the lengths, which only the device reads, may
+ * turn a call to wave slices.
+ */
+neo_status neo_debug_division(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads,
+                              int32_t head_dim, int32_t max_blocks_per_seq, int32_t variant,
+                              int32_t max_slices, int32_t compute_units, int32_t* division);
+
 /* Message of this thread's last non-OK status; valid until its next neo_* call. */
 const char* neo_last_error(void);
 

@@ -35,6 +35,7 @@ __all__ = [
     "new_workspace", "kv_append", "copy_blocks", "cpu_decode_attention", "CPU_ISAS",
     "cpu_best_isa", "cpu_default_threads", "cpu_read_probe", "cpu_kv_append",
     "read_probe", "read_probe_tiles", "READ_PROBE_SINK_WORDS", "new_kv_cache",
+    "debug_division", "DIVISIONS",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -47,6 +48,8 @@ MAX_SLICES = 4096
 READ_PROBE_SINK_WORDS = 16384
 STATUS = {0: "NEO_OK", 1: "NEO_ERR_INVALID_ARG", 2: "NEO_ERR_UNSUPPORTED",
           3: "NEO_ERR_WORKSPACE", 4: "NEO_ERR_HIP"}
+
+DIVISIONS = ("wave_slices", "head_slices", "pairs", "units", "whole")
 
 _lib = None
 _lock = threading.Lock()
@@ -130,6 +133,8 @@ def load_library():
         lib.neo_cpu_default_threads.restype = ctypes.c_int32
         lib.neo_debug_validate.argtypes = [P, P, I, I, I, I, P, P]
         lib.neo_debug_validate.restype = ctypes.c_int
+        lib.neo_debug_division.argtypes = [I, I, I, I, I, I, I, I, ctypes.POINTER(I)]
+        lib.neo_debug_division.restype = ctypes.c_int
         lib.neo_last_error.argtypes = []
         lib.neo_last_error.restype = ctypes.c_char_p
         lib.neo_version.argtypes = []
@@ -422,6 +427,20 @@ def debug_validate(block_table, seq_lens, num_blocks: int, block_size: int = 16,
                                       seq_lens.shape[0], block_table.shape[1], int(block_size),
                                       int(num_blocks), cnt.data_ptr(), sh))
     return int(cnt.item())
+
+
+def debug_division(batch: int, num_q_heads: int, num_kv_heads: int, max_blocks_per_seq: int, *,
+                   head_dim: int = 128, variant: str = "auto", max_slices: int = 0,
+                   compute_units: int = 256) -> str:
+    """How a ``decode_attention`` call of these shapes is divided (one of ``DIVISIONS``).
+    Host only: with "head_slices", "units" and "whole" the lengths may turn a
+    call to wave slices on the device."""
+    out = ctypes.c_int32(0)
+    _check(load_library().neo_debug_division(int(batch), int(num_q_heads), int(num_kv_heads),
+                                             int(head_dim), int(max_blocks_per_seq),
+                                             VARIANTS[variant], int(max_slices),
+                                             int(compute_units), ctypes.byref(out)))
+    return DIVISIONS[out.value]
 
 
 def kv_append(k_cache, v_cache, k_new, v_new, block_table, seq_lens, *, stream=None):

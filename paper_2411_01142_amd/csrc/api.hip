@@ -12,6 +12,7 @@
 #include "neo_error.h"
 #include "kv_ops.h"
 #include "neo_internal.h"
+#include "route.h"
 
 
 namespace {
@@ -188,77 +189,6 @@ neo_status check_decode(const void* q, const void* k_cache, const void* v_cache,
   return NEO_OK;
 }
 
-// How a call is divided (SliceMode, and for kPairs the workgroups of a pair and
-// the order of the requests), from what the host knows: the batch, the heads
-// and the table's width (mbps), which bounds the lengths. A caller's slice cap
-// is a cap on wavefronts' slices.
-struct Route {
-  neo::SliceMode mode;
-  int32_t parts, longest_first;
-};
-
-// kPairs: every pair gets the same workgroups whatever its length, so it suits
-// batches whose longest pair cannot keep few workgroups busy long after the
-// others are done. Up to 32 pairs always (one request of 30000 tokens among 31
-// short ones, one kv head: 219 us planned, 24 here), and up to four pairs per
-// compute unit while a workgroup has at most 128 blocks (about 14 us of
-// reading), or 256 where the pairs run in rounds, longest first (512 pairs of
-// U[256, 4096] tokens: 106 us planned, 95 here; 256 pairs in one round,
-// lognormal around 1000 and up to 4000: 37.5 planned, 40.7 here). Up to eight
-// pairs per compute unit if they have room to be long enough for a workgroup's
-// start (2048 pairs of U[512, 2048] tokens 210 planned, 201 here; of U[50, 200]
-// 30 and 35; 2000 of U[100, 1000] 103 and 112); more pairs stream better in
-// slices (4096 of U[256, 4096]: 681 and 696). A pair of at most 32 blocks is not worth a merge (19
-// blocks: 6.8 us by one workgroup, 8.3 by two) or an order (64 requests of
-// U[50, 150] tokens: 9.7 in index order, 11.7 longest first). Workgroups
-// beyond one per compute unit run in rounds, so the second one is given only
-// where a pair then has at least four (96 pairs of up to 500 blocks: 57 us
-// planned, 51 with two workgroups, 45 with five; 256 pairs of up to 250: 57
-// with one, 59 with two).
-constexpr int32_t kPairsAlways = 32;
-constexpr int32_t kPairsPerCu = 4;
-constexpr int32_t kLongPairsPerCu = 8;
-constexpr int32_t kLongPairBlocksMin = 128;
-constexpr int32_t kPairBlocksPerPart = 128;
-constexpr int32_t kPairBlocksOrdered = 256;
-constexpr int32_t kPairShortBlocks = 32;
-
-// Head slices need whole groups of four kv heads, and pay once every compute
-// unit has a few (request, four heads) pairs with some blocks to stream: below
-// that a slice is a part of one or two pairs and the cut pairs' partials all
-// cross workgroups, where wave slices merge most of them in LDS. Measured, wave
-// / head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512,
-// 2048] tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512
-// of U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50,
-// 200] tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52
-// blocks) 53.9 / 54.0.
-constexpr int32_t kHeadPairsPerCu = 2;
-constexpr int32_t kHeadBlocksPerCu = 64;
-
-Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int32_t mbps,
-            int32_t cus) {
-  if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {neo::kWaveSlices, 0, 0};
-  const int64_t pairs = (int64_t)batch * hkv;
-  if (pairs <= (int64_t)kPairsPerCu * cus ||
-      (pairs <= (int64_t)kLongPairsPerCu * cus && mbps >= kLongPairBlocksMin)) {
-    const int32_t chunks = (mbps - 1) / neo::kPairChunk + 1;
-    const int32_t n = (int32_t)pairs, c = std::min(cus, NEO_MAX_SLICES / 8);
-    int32_t parts = mbps <= kPairShortBlocks ? 1 : std::max(1, std::min(c / n, chunks));
-    if (mbps / kPairBlocksPerPart >= parts && n <= c / 2) parts = std::min(2 * c / n, chunks);
-    const bool ordered = n > cus && mbps > kPairShortBlocks && batch <= neo::kMaxOrderedBatch;
-    if (n <= kPairsAlways || (ordered && mbps <= kPairBlocksOrdered) ||
-        (n <= kPairsPerCu * cus && mbps <= (int64_t)kPairBlocksPerPart * parts))
-      return {neo::kPairs, parts, ordered};
-  }
-  if (hkv % neo::kHeadsPerSlice == 0) {
-    const int64_t groups = pairs / neo::kHeadsPerSlice;
-    if (groups >= (int64_t)kHeadPairsPerCu * cus &&
-        groups * mbps >= (int64_t)kHeadBlocksPerCu * cus)
-      return {neo::kHeadSlices, 0, 0};
-  }
-  return {neo::kWaveSlices, 0, 0};
-}
-
 // ----------------------------------------------------------------- static scratch
 //
 // The allocation-free entry point keeps the fused kernel's cross-workgroup
@@ -269,10 +199,10 @@ Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int
 // plan of that entry point uses at most kScratchSlices slices (one per wave
 // of one 4-wave workgroup per CU on a 256-CU part). Every GPU the library
 // runs on holds one copy until the process ends (16.1 MiB).
-// A plan without slices (kPairs) uses a counter per pair and a partial slot per
-// workgroup of a pair, at most 2 NEO_MAX_SLICES / 8 of each.
+// A call without slices (kPairs, kUnits, kWhole) uses a counter per pair and a
+// partial slot per workgroup, at most one of each per compute unit.
 constexpr int32_t kScratchSlices = 1024;
-static_assert(2 * (NEO_MAX_SLICES / 8) <= kScratchSlices, "kPairs must fit the scratch");
+static_assert(neo::kMaxCus <= kScratchSlices, "calls without slices must fit the scratch");
 constexpr int32_t kScratchMaxGroup = 16;
 constexpr size_t kScratchCountersOff = 0;
 constexpr size_t kScratchLseOff =
@@ -376,7 +306,8 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
                               : schedule == NEO_SCHEDULE_STAGED   ? neo::kStaged
                                                                   : neo::kFused;
 
-  const Route r = route(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq, cus);
+  const neo::Route r =
+      neo::route(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq, cus);
 
   char* ws = static_cast<char*>(workspace);
   neo::DecodeParams p;
@@ -401,14 +332,16 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
   p.slice_quantum = quantum;
   p.xcd8 = xcds == 8;
   p.parts = r.parts;
-  p.longest_first = r.longest_first;
+  p.units = r.units;
+  p.grid_y = r.grid_y;
+  p.cus = cus;
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   // A call without slices has nothing to plan or combine.
-  if (sched == neo::kStaged && r.mode != neo::kPairs) {
+  if (sched == neo::kStaged && neo::has_plan(r.mode)) {
     e = neo::launch_plan(seq_lens, batch, num_kv_heads, max_blocks_per_seq, slices, min_tiles,
                          quantum, p.xcd8, r.mode, reinterpret_cast<neo::PlanHeader*>(ws + wl.hdr),
                          reinterpret_cast<neo::SliceStart*>(ws + wl.starts),
@@ -427,7 +360,7 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
     e = hipEventRecord(static_cast<hipEvent_t>(decode_end_event), s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "event record: %s", hipGetErrorString(e));
   }
-  if (sched != neo::kFused && r.mode != neo::kPairs) {
+  if (sched != neo::kFused && neo::has_plan(r.mode)) {
     e = neo::launch_combine(p, group, r.mode, grid, s);
     if (e != hipSuccess) return set_error(NEO_ERR_HIP, "combine launch: %s", hipGetErrorString(e));
   }
@@ -514,9 +447,12 @@ neo_status neo_decode_attention_noalloc(const void* q, const void* k_cache, cons
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
   const int32_t grid = (slices + neo::kWavesPerGroup - 1) / neo::kWavesPerGroup;
-  const Route r = route(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus);
+  const neo::Route r =
+      neo::route(NEO_VARIANT_MFMA, 0, batch, num_kv_heads, max_blocks_per_seq, cus);
   p.parts = r.parts;
-  p.longest_first = r.longest_first;
+  p.units = r.units;
+  p.grid_y = r.grid_y;
+  p.cus = cus;
   const hipError_t e = neo::launch_decode_mfma(p, group, r.mode, neo::kFused, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   return ok();
@@ -717,6 +653,26 @@ neo_status neo_debug_validate(const int32_t* block_table, const int32_t* seq_len
                                       block_size, num_blocks, error_count,
                                       static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "validate launch: %s", hipGetErrorString(e));
+  return ok();
+}
+
+static_assert((int)neo::kWaveSlices == NEO_DIVISION_WAVE_SLICES &&
+                  (int)neo::kHeadSlices == NEO_DIVISION_HEAD_SLICES &&
+                  (int)neo::kPairs == NEO_DIVISION_PAIRS &&
+                  (int)neo::kUnits == NEO_DIVISION_UNITS && (int)neo::kWhole == NEO_DIVISION_WHOLE,
+              "neo_division names SliceMode");
+
+neo_status neo_debug_division(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads,
+                              int32_t head_dim, int32_t max_blocks_per_seq, int32_t variant,
+                              int32_t max_slices, int32_t compute_units, int32_t* division) {
+  if (!division) return set_error(NEO_ERR_INVALID_ARG, "division is NULL");
+  const neo_status st = check_heads(num_q_heads, num_kv_heads, head_dim);
+  if (st != NEO_OK) return st;
+  if (batch <= 0 || max_blocks_per_seq <= 0 || compute_units <= 0 || max_slices < 0)
+    return set_error(NEO_ERR_INVALID_ARG, "sizes must be positive");
+  if (variant == NEO_VARIANT_AUTO) variant = NEO_VARIANT_MFMA;
+  *division = neo::route(variant, max_slices, batch, num_kv_heads, max_blocks_per_seq,
+                         compute_units).mode;
   return ok();
 }
 

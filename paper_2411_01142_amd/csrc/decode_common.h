@@ -230,6 +230,10 @@ __device__ inline int32_t wave_incl_scan_i32(int32_t v) {
 __device__ inline int32_t wave_sum_i32(int32_t v) {
   return __builtin_amdgcn_readlane(wave_incl_scan_i32(v), kWave - 1);
 }
+__device__ inline int32_t wave_max_i32(int32_t v) {
+  return __builtin_amdgcn_readlane(
+      wave_scan_bits(v, INT32_MIN, [](int32_t a, int32_t b) { return max(a, b); }), kWave - 1);
+}
 __device__ inline float wave_max_f32(float v) {
   const int32_t s = wave_scan_bits(
       __builtin_bit_cast(int32_t, v), __builtin_bit_cast(int32_t, -INFINITY),
@@ -353,21 +357,29 @@ __device__ inline void load_weights(const DecodeParams& p, int base, int lane,
     w[r] = (base + r * kWave + lane < p.batch) ? pair_weight(raw[r], p.mbps, kMode) : 0;
 }
 
+// The positions of all requests; w and raw: the last kPlanChunk requests'.
+constexpr int kPlanChunk = kWave * kPlanRegs;
 template <SliceMode kMode>
-__device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int slice, int lane) {
-  SliceInfo si;
-  const int32_t hk = pairs_per_request(p.hkv, kMode);
-  constexpr int kChunk = kWave * kPlanRegs;
-  int32_t w[kPlanRegs], raw[kPlanRegs];
+__device__ inline int32_t plan_total(const DecodeParams& p, int lane, int32_t (&w)[kPlanRegs],
+                                     int32_t (&raw)[kPlanRegs]) {
   int32_t total = 0;
-  for (int base = 0; base < p.batch; base += kChunk) {
+  for (int base = 0; base < p.batch; base += kPlanChunk) {
     load_weights<kMode>(p, base, lane, w, raw);
     int32_t s = 0;
 #pragma unroll
     for (int r = 0; r < kPlanRegs; ++r) s += w[r];
     total += wave_sum_i32(s);
   }
-  const int32_t W = uniform(total * hk);
+  return uniform(total * pairs_per_request(p.hkv, kMode));
+}
+
+// The slice, from plan_total's results.
+template <SliceMode kMode>
+__device__ inline SliceInfo plan_slice(const DecodeParams& p, int slice, int lane, int32_t W,
+                                       int32_t (&w)[kPlanRegs], int32_t (&raw)[kPlanRegs]) {
+  SliceInfo si;
+  const int32_t hk = pairs_per_request(p.hkv, kMode);
+  constexpr int kChunk = kPlanChunk;
   si.geo = make_uniform(
       plan_geom(W, slice_count(W, p.min_tiles, p.max_slices, p.slice_quantum, kMode), p.xcd8 != 0,
                 kMode));
@@ -426,6 +438,13 @@ __device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int slice, int l
   si.x = rem % found_w;
   si.L = clamp_len(found_len, p.mbps);
   return make_uniform(si);
+}
+
+template <SliceMode kMode>
+__device__ inline SliceInfo plan_in_wave(const DecodeParams& p, int slice, int lane) {
+  int32_t w[kPlanRegs], raw[kPlanRegs];
+  const int32_t W = plan_total<kMode>(p, lane, w, raw);
+  return plan_slice<kMode>(p, slice, lane, W, w, raw);
 }
 
 // ----------------------------------------------------------------- outputs
@@ -724,21 +743,32 @@ __device__ inline void merge_cut(const DecodeParams& p, int32_t b, int32_t g, in
     merge_pair<G, true>(p, p.part_o, p.part_lse, 0, b, g, first_tile, c0, c1, cuts, lane);
 }
 
+// The slice of this wavefront of workgroup `index`, and the length of the
+// request of its number for zero_empty_rows (requested before the plan's).
+template <Schedule kSched>
+__device__ inline SliceInfo plan_wave_slice(const DecodeParams& p, int32_t index, int32_t* len0) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = index * kWavesPerGroup + (threadIdx.x >> 6);
+  *len0 = wave < p.batch ? p.lens[wave] : 0;
+  return kSched == kStaged ? read_plan<kWaveSlices>(p, wave)
+                           : plan_in_wave<kWaveSlices>(p, wave, lane);
+}
+
 // Family provides: Tile, State, Q, Shared; load_q, init, load_tile, step, write.
-// PF tiles are in flight ahead of the one being computed.
+// PF tiles are in flight ahead of the one being computed. Run by the first four
+// wavefronts of workgroup `index` of `workgroups`; si and len0: plan_wave_slice.
 template <class F, int G, int PF, Schedule kSched>
-__device__ inline void decode_driver(const DecodeParams& p) {
+__device__ inline void decode_driver(const DecodeParams& p,
+                                     typename GroupMergeOf<G, kSched == kFused>::type& gm,
+                                     int32_t index, int32_t workgroups, const SliceInfo& si,
+                                     int32_t len0) {
   constexpr bool kMergeHere = kSched == kFused;  // merge cut pairs in this kernel
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = threadIdx.x >> 6;
-  const int wave = blockIdx.x * kWavesPerGroup + wv;
-  const int nwaves = gridDim.x * kWavesPerGroup;
-  const int32_t len0 = wave < p.batch ? p.lens[wave] : 0;
+  const int wave = index * kWavesPerGroup + wv;
+  const int nwaves = workgroups * kWavesPerGroup;
   // Slices of this workgroup: first_slice .. first_slice + kWavesPerGroup - 1.
-  const int32_t first_slice = blockIdx.x * kWavesPerGroup;
-  __shared__ typename GroupMergeOf<G, kMergeHere>::type gm;
-  const SliceInfo si = kSched == kStaged ? read_plan<kWaveSlices>(p, wave)
-                                          : plan_in_wave<kWaveSlices>(p, wave, lane);
+  const int32_t first_slice = index * kWavesPerGroup;
   zero_empty_rows(p, wave, nwaves, lane, len0);
   // Merges through LDS pay when slices are long enough to hold cut segments
   // of several tiles; for tiny slices the barrier that clears the counters

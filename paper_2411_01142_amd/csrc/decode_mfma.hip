@@ -268,7 +268,10 @@ __global__ __launch_bounds__(kWave * kWavesPerGroup, kMode == kHeadSlices ? 1 : 
     // One tile in flight ahead of the one being computed: with 4 waves on every
     // CU that keeps HBM saturated; deeper prefetch measured equal or slower
     // (more requests in flight lower the HBM efficiency).
-    decode_driver<MfmaFamily<G>, G, 1, kSched>(p);
+    __shared__ typename GroupMergeOf<G, kSched == kFused>::type gm;
+    int32_t len0;
+    const SliceInfo si = plan_wave_slice<kSched>(p, blockIdx.x, &len0);
+    decode_driver<MfmaFamily<G>, G, 1, kSched>(p, gm, blockIdx.x, gridDim.x, si, len0);
   }
 }
 
@@ -282,6 +285,26 @@ __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_pair_kernel(
   p.table = table;
   p.mbps = mbps;
   pair_driver<MfmaFamily<G>, G>(p);
+}
+
+template <int G>
+__global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_unit_kernel(
+    const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
+  p.lens = lens;
+  p.batch = batch;
+  p.hkv = hkv;
+  p.mbps = mbps;
+  unit_driver<MfmaFamily<G>, G>(p);
+}
+
+template <int G, bool kTwoRounds>
+__global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_whole_kernel(
+    const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
+  p.lens = lens;
+  p.batch = batch;
+  p.hkv = hkv;
+  p.mbps = mbps;
+  whole_driver<MfmaFamily<G>, G, kTwoRounds>(p);
 }
 
 template <int G, SliceMode kMode>
@@ -307,6 +330,19 @@ hipError_t launch_mode(const DecodeParams& p, SliceMode mode, Schedule sched, in
   if (mode == kPairs) {
     decode_pair_kernel<G><<<dim3(p.parts, p.hkv, p.batch), kWave * kPairWaves, 0, stream>>>(
         p.lens, p.table, p.mbps, p);
+    return hipGetLastError();
+  }
+  if (mode == kUnits) {
+    decode_unit_kernel<G><<<dim3(p.hkv, p.grid_y), kWave * kPairWaves, 0, stream>>>(
+        p.lens, p.batch, p.hkv, p.mbps, p);
+    return hipGetLastError();
+  }
+  if (mode == kWhole) {
+    const dim3 grid2(p.hkv, p.grid_y), block(kWave * kPairWaves);
+    if ((int64_t)p.batch * p.hkv > p.cus)
+      decode_whole_kernel<G, true><<<grid2, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+    else
+      decode_whole_kernel<G, false><<<grid2, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
     return hipGetLastError();
   }
   return mode == kHeadSlices ? launch_g<G, kHeadSlices>(p, sched, grid, stream)

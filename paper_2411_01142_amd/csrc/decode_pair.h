@@ -1,52 +1,68 @@
-// The matrix-core family's kernel for small batches: nothing is planned; the
-// `parts` workgroups of each (request, kv head) pair know their blocks from
-// their own index.
+// The matrix-core family's kernels for small batches, in which a workgroup of
+// eight wavefronts takes one (request, kv head) pair or a part of one.
 //
 // What bounds a small call is its chain of dependent steps, not its bytes. A
 // planned call reads every length, finds its slice, reads the block ids, then
 // the tiles, writes a partial, counts it, and one wavefront merges a pair's
 // partials, up to 128 of them, in as many dependent rounds as its registers
-// need. Here lengths, block ids and query rows are read together, eight
-// wavefronts share a workgroup's blocks and merge in LDS, and what is left to
-// merge across workgroups is one partial for each of a pair's `parts`, merged
-// by a whole workgroup, a head per wavefront.
+// need. Here eight wavefronts share a workgroup's blocks and merge in LDS, and
+// what is left to merge across workgroups is one partial for each of a pair's
+// few, merged by a whole workgroup, a head per wavefront.
+//
+// Three divisions (the host chooses one, from what it knows):
+//  kPairs: the host's own, the same workgroups for every pair. Lengths, block
+//    ids and query rows are read together.
+//  kUnits: pairs cut into units of one size, found from all lengths.
+//  kWhole: one workgroup per pair, if all lengths make that a good division.
+// The last two must not depend on the table's width, which says little about
+// the lengths. They take wave slices instead where the lengths make their own
+// division a bad one: a workgroup with far more than its share of the blocks
+// reads them alone while the others are done.
 //
 // One compute unit reads about 77 GB/s of tiles however many of its wavefronts
 // ask (2 MB by each of 8 workgroups alone: 27 us with 4, 8 or 16 wavefronts,
-// one or two tiles a step), which is what `parts` is for. Eight wavefronts
-// with one tile in flight measured best: with more prefetch or at the 128
-// registers of two workgroups per compute unit (which spills) calls are 10-60 %
-// longer; with four, equal when small and 5 % longer at 512 pairs. Chunks of
-// 16 blocks: with 32, one request of 877 tokens takes 9.7 us instead of 7.7.
+// one or two tiles a step). Eight wavefronts with one tile in flight measured
+// best: with more prefetch or at the 128 registers of two workgroups per
+// compute unit (which spills) calls are 10-60 % longer; with four, equal when
+// small and 5 % longer at 512 pairs. Chunks of 16 blocks: with 32, one request
+// of 877 tokens takes 9.7 us instead of 7.7.
 //
 // Measured (device time of a call, planned slices -> here, 32 / 8 heads):
-// one request of 877 tokens 13.0 -> 7.7 us, of 50021 59 -> 37 us; 4 requests
-// of U[64, 512] with 32 / 32 heads 10.0 -> 8.4; 13 of U[100, 1500] 16.5 ->
-// 13.8; 64 of U[512, 2048] 65.6 -> 61.0 (128 / 8 heads: 72 -> 59).
+//  kPairs: one request of 877 tokens 12.8 -> 7.8 us, of 50021 59 -> 36; 4
+//    requests of U[64, 512] with 32 / 32 heads 9.6 -> 8.1; 64 of U[50, 150]
+//    13.3 -> 9.6.
+//  kUnits, tables of 500 blocks: 13 requests of U[100, 1500] 15.9 -> 12.5, 5 of
+//    U[50, 150] 8.8 -> 5.7, 5 of 8000 tokens 37.4 -> 30.5, one of 8000 among 12
+//    of U[75, 150] 31.4 -> 13.6. (Two fixed workgroups a pair: 14.8, 4.9, 30.2
+//    and 24.0.)
+//  kWhole: 64 of U[512, 2048] 58 -> 52, 64 of 2048 tokens 88.5 -> 84, 32 of
+//    U[100, 1000] 19.7 -> 16.2; 512 of U[256, 4096] with 8 / 1 heads 102 -> 90.
+//    Where it takes wave slices: one of 4096 among 64 of U[75, 150] 20.6 -> 21.1
+//    (whole pairs 41.6), 64 lognormal around 500 34.0 -> 34.5 (44.2).
 #pragma once
 
 #include "decode_common.h"
 
 namespace neo {
 
-// One head of a pair from the partials of `k` workgroups (workspace slots
-// slot0 .. slot0 + k - 1): the exact log-sum-exp merge in the order of the
-// slots. Lane l owns dims 2l, 2l + 1.
-template <int G>
-__device__ inline float2 merge_parts(const DecodeParams& p, int32_t slot0, int32_t k, int h,
+// One head of a pair from the partials of `k` workgroups, the i-th of them in
+// workspace slot slot_of(i): the exact log-sum-exp merge in that order. Lane l
+// owns dims 2l, 2l + 1.
+template <int G, class SlotOf>
+__device__ inline float2 merge_parts(const DecodeParams& p, SlotOf slot_of, int32_t k, int h,
                                      int lane) {
   constexpr int kBatch = 16;
   float m = kLowest, z = 0.f, x = 0.f, y = 0.f;
   for (int32_t base = 0; base < k; base += kWave) {
     const int32_t cnt = min(kWave, k - base);
-    const float got = load_coherent(p.part_lse + (slot0 + base + min(lane, cnt - 1)) * G + h);
+    const float got = load_coherent(p.part_lse + slot_of(base + min(lane, cnt - 1)) * G + h);
     const float lse = lane < cnt ? got : -INFINITY;
     float2 v[kBatch];
     auto load = [&](int32_t i0) {
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
         v[u] = load_coherent2(
-            p.part_o + ((size_t)(slot0 + base + min(i0 + u, cnt - 1)) * G + h) * kHeadDim + 2 * lane);
+            p.part_o + ((size_t)slot_of(base + min(i0 + u, cnt - 1)) * G + h) * kHeadDim + 2 * lane);
     };
     load(0);
     const float mc = fmaxf(m, wave_max_f32(lse));
@@ -72,97 +88,20 @@ __device__ inline float2 merge_parts(const DecodeParams& p, int32_t slot0, int32
   return float2{x * inv, y * inv};
 }
 
-// The request of rank r when requests are taken longest first, to within a
-// sixteenth of the table's width (ties in index order). Pairs beyond one per
-// compute unit run in rounds, and the call ends with the last workgroup: with
-// long pairs first the short ones fill the ends. Every workgroup finds its
-// request by itself: 64 lengths a wavefront, a ballot for each of 16 classes,
-// a scan over the classes' counts; about a microsecond per round. Measured,
-// index order / longest first: 64 requests of U[512, 2048] tokens, 8 kv heads
-// 57.7 / 55.9 us, of lognormal lengths around 500 33.8 / 28.4, 40 of U[512,
-// 2048] 41.3 / 35.9, one of 2000 among 127 of 100 33.5 / 25.0, 128 of nearly
-// equal lengths 97.8 / 100.0.
-constexpr int kLengthClasses = 16;
-__device__ inline int32_t request_of_rank(const DecodeParams& p, int32_t r, int lane, int wv) {
-  __shared__ uint64_t members[kLengthClasses * (kMaxOrderedBatch / kWave)];  // [class][64 requests]
-  const int32_t groups = (p.batch + kWave - 1) / kWave;
-  const int32_t shift = max(0, 28 - __clz(p.mbps));  // mbps >> shift is below 16
-  for (int32_t gr = wv; gr < groups; gr += kPairWaves) {
-    const int32_t i = gr * kWave + lane;
-    const int32_t cls =
-        i < p.batch ? kLengthClasses - 1 - (blocks_of(p.lens[i], p.mbps) >> shift) : -1;
-    uint64_t mine = 0;
-#pragma unroll
-    for (int k = 0; k < kLengthClasses; ++k) {
-      const uint64_t m = __ballot(cls == k);
-      if (lane == k) mine = m;
-    }
-    if (lane < kLengthClasses) members[lane * groups + gr] = mine;
-  }
-  __syncthreads();
-  const int32_t entries = groups * kLengthClasses;
-  int32_t before = 0;
-  for (int32_t base = 0; base < entries; base += kWave) {
-    const uint64_t m = base + lane < entries ? members[base + lane] : 0;
-    const int32_t c = __popcll(m);
-    const int32_t incl = before + wave_incl_scan_i32(c);
-    const uint64_t hit = __ballot(incl > r);
-    if (hit) {
-      // The entry holding rank r, and in it the request with that many
-      // members below it.
-      const int e = __ffsll((unsigned long long)hit) - 1;
-      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m, e);
-      const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m >> 32), e);
-      const int32_t want =
-          r - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(c, e));
-      const int32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-      const bool member = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1;
-      const uint64_t at = __ballot(member && below == want);
-      return (base + e) % groups * kWave + __ffsll((unsigned long long)at) - 1;
-    }
-    before = __builtin_amdgcn_readlane(incl, kWave - 1);
-  }
-  return 0;  // not reached: r is below the batch
-}
-
-// Workgroup (s, g, b) takes chunks s, s + parts, s + 2 parts, ... of pair
-// (b, g); in a chunk wavefront w takes tiles w, w + kPairWaves, ...
-template <class F, int G>
-__device__ inline void pair_driver(const DecodeParams& p) {
+// The eight wavefronts of a workgroup over its share of pair (b, g): wavefront
+// wv computes tiles 0 .. n - 1, the i-th of them block block_of(i); `ids` holds
+// the physical ids of the first 64, one per lane. `shares`: wavefronts with
+// tiles (the first ones). The pair has k workgroups with tiles, whose partials
+// are in slots slot_of(0) .. slot_of(k - 1), this workgroup's in `slot`.
+template <class F, int G, class BlockOf, class SlotOf>
+__device__ inline void pair_body(const DecodeParams& p, int32_t b, int32_t g, int32_t L, int32_t n,
+                                 int shares, int32_t ids, const typename F::Q& q, BlockOf block_of,
+                                 int32_t k, int32_t slot, SlotOf slot_of, int lane, int wv) {
   __shared__ float rows[kPairWaves][G * kHeadDim];  // unnormalised, staged as by F::stage
   __shared__ float ms[kPairWaves][G], ls[kPairWaves][G];
   __shared__ int32_t arrived;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wv = uniform(threadIdx.x >> 6);
-  const int32_t s = blockIdx.x, g = blockIdx.y, parts = gridDim.x;
-  const int32_t b =
-      p.longest_first ? uniform(request_of_rank(p, blockIdx.z, lane, wv)) : (int32_t)blockIdx.z;
-  // Block of this wavefront's i-th tile.
-  auto block_of = [&](int32_t i) -> int32_t {
-    return kPairChunk * (s + parts * (i / kPairTilesPerWave)) + wv +
-           kPairWaves * (i % kPairTilesPerWave);
-  };
-  // The length, the block ids and the query rows do not wait for one another.
-  const int32_t raw = p.lens[b];
   const int32_t* row = p.table + (size_t)b * p.mbps;
-  int32_t ids = row[min(block_of(lane), p.mbps - 1)];
-  typename F::Q q;
-  F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
   float* out = p.out + ((size_t)b * p.hq + g * G) * kHeadDim;
-  const int32_t L = clamp_len(uniform(raw), p.mbps);
-  const int32_t nb = (L + kBlock - 1) / kBlock;
-  const int32_t chunks = (nb + kPairChunk - 1) / kPairChunk;
-  if (s >= chunks) {  // no block for this workgroup
-    if (nb == 0 && s == 0)
-      for (int i = threadIdx.x; i < G * kHeadDim; i += kPairWaves * kWave) out[i] = 0.f;
-    return;
-  }
-  // Tiles of this wavefront: all of the workgroup's chunks but the last are whole.
-  const int32_t last = (chunks - 1 - s) / parts;
-  const int32_t rem = nb - kPairChunk * (s + parts * last);  // blocks from the last chunk on
-  const int32_t n = kPairTilesPerWave * last +
-                    min(kPairTilesPerWave, max(0, (rem - wv + kPairWaves - 1) / kPairWaves));
-  const int shares = last > 0 ? kPairWaves : min(kPairWaves, rem);  // wavefronts with tiles
   if (n > 0) {
     const size_t blk_stride = (size_t)p.blk_stride;
     int32_t base = 0;  // first tile whose id is in ids
@@ -202,9 +141,6 @@ __device__ inline void pair_driver(const DecodeParams& p) {
     }
   }
   __syncthreads();
-  const int32_t k = min(parts, chunks);  // workgroups with blocks of this pair
-  const int32_t pair = b * p.hkv + g;
-  const int32_t slot = pair * parts + s;
   for (int h = wv; h < G; h += kPairWaves) {
     float m = kLowest, l = 0.f, x = 0.f, y = 0.f;
     for (int w = 0; w < shares; ++w) m = fmaxf(m, ms[w][h]);
@@ -227,6 +163,7 @@ __device__ inline void pair_driver(const DecodeParams& p) {
   if (k == 1) return;
   // Every wavefront's stores are complete before the workgroup is counted; the
   // last workgroup of the pair merges it and leaves the counter at zero.
+  const int32_t pair = b * p.hkv + g;
   wait_all_memory();
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -240,7 +177,331 @@ __device__ inline void pair_driver(const DecodeParams& p) {
   if (arrived != k - 1) return;
   for (int h = wv; h < G; h += kPairWaves)
     *reinterpret_cast<float2*>(out + h * kHeadDim + 2 * lane) =
-        merge_parts<G>(p, pair * parts, k, h, lane);
+        merge_parts<G>(p, slot_of, k, h, lane);
+}
+
+// The output rows of pair (b, g), which has no tokens.
+template <int G>
+__device__ inline void zero_pair(const DecodeParams& p, int32_t b, int32_t g) {
+  float* out = p.out + ((size_t)b * p.hq + g * G) * kHeadDim;
+  for (int i = threadIdx.x; i < G * kHeadDim; i += kPairWaves * kWave) out[i] = 0.f;
+}
+
+// kPairs. Workgroup (s, g, b) takes chunks s, s + parts, s + 2 parts, ... of
+// pair (b, g); in a chunk wavefront w takes tiles w, w + kPairWaves, ...
+template <class F, int G>
+__device__ inline void pair_driver(const DecodeParams& p) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = uniform(threadIdx.x >> 6);
+  const int32_t s = blockIdx.x, g = blockIdx.y, b = blockIdx.z, parts = gridDim.x;
+  // Block of this wavefront's i-th tile.
+  auto block_of = [&](int32_t i) -> int32_t {
+    return kPairChunk * (s + parts * (i / kPairTilesPerWave)) + wv +
+           kPairWaves * (i % kPairTilesPerWave);
+  };
+  // The length, the block ids and the query rows do not wait for one another.
+  const int32_t raw = p.lens[b];
+  const int32_t ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
+  typename F::Q q;
+  F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
+  const int32_t L = clamp_len(uniform(raw), p.mbps);
+  const int32_t nb = (L + kBlock - 1) / kBlock;
+  const int32_t chunks = (nb + kPairChunk - 1) / kPairChunk;
+  if (s >= chunks) {  // no block for this workgroup
+    if (nb == 0 && s == 0) zero_pair<G>(p, b, g);
+    return;
+  }
+  // Tiles of this wavefront: all of the workgroup's chunks but the last are whole.
+  const int32_t last = (chunks - 1 - s) / parts;
+  const int32_t rem = nb - kPairChunk * (s + parts * last);  // blocks from the last chunk on
+  const int32_t n = kPairTilesPerWave * last +
+                    min(kPairTilesPerWave, max(0, (rem - wv + kPairWaves - 1) / kPairWaves));
+  const int shares = last > 0 ? kPairWaves : min(kPairWaves, rem);
+  const int32_t slot0 = (b * p.hkv + g) * parts;
+  pair_body<F, G>(p, b, g, L, n, shares, ids, q, block_of, min(parts, chunks), slot0 + s,
+                  [&](int32_t i) { return slot0 + i; }, lane, wv);
+}
+
+// Blocks that the busiest workgroup of a call without slices may have beyond an
+// even share (`even`) of all blocks before wave slices are the better division.
+// It reads them while others are done, at 0.106 us each. Wave slices spend about
+// 4 us more on plans and ends, stream an even share about 4 % more slowly, and
+// merge a pair of `longest` blocks from its cuts at 32 rows a round trip of
+// 0.8 us.
+constexpr float kLoneBlocks = 40.f;
+constexpr float kLoneBlocksOfEven = 0.125f;
+constexpr float kLoneBlocksPerRow = 0.25f;
+template <int G>
+__device__ inline float lone_slack(const DecodeParams& p, float even, int32_t W, int32_t longest) {
+  const float slices =
+      (float)slice_count(W, p.min_tiles, p.max_slices, p.slice_quantum, kWaveSlices);
+  return kLoneBlocks + kLoneBlocksOfEven * even +
+         kLoneBlocksPerRow * G * (float)longest * slices / (float)max(W, 1);
+}
+
+// Lengths of the first 64 kSets requests, 64 t + lane in raw[t] (0 past the
+// batch): straight-line code, since a branch would make the compiler wait for
+// what is requested after them.
+template <int kSets>
+__device__ inline void load_lens(const DecodeParams& p, int lane, int32_t* raw) {
+#pragma unroll
+  for (int t = 0; t < kSets; ++t) raw[t] = p.lens[min(kWave * t + lane, p.batch - 1)];
+}
+
+// kUnits: every pair is cut into units of S blocks, the last one shorter, and
+// the units of all pairs run at once, one per compute unit. A kv head's units
+// are numbered alike, request after request, and workgroup (g, v) takes unit v
+// of kv head g.
+struct Unit {
+  int32_t b, L;
+  int32_t first, blocks;  // its blocks: first .. first + blocks - 1
+  int32_t unit0, units;   // the units of its pair
+};
+enum UnitFound { kUnitFound, kNoUnit, kBadDivision };
+
+// Unit v. S is the smallest of 64 sizes that gives at most p.units units (the
+// grid has one for every request). Every wavefront finds S and the unit by
+// itself from all lengths.
+constexpr int kUnitSets = kUnitMaxBatch / kWave;
+template <int G>
+__device__ inline UnitFound find_unit(const DecodeParams& p, int32_t v, Unit& u, int lane,
+                                      const int32_t* raw) {
+  int32_t L[kUnitSets], nb[kUnitSets];
+  int32_t sum = 0, most = 0, weights = 0;
+#pragma unroll
+  for (int t = 0; t < kUnitSets; ++t) {
+    L[t] = kWave * t + lane < p.batch ? clamp_len(raw[t], p.mbps) : 0;
+    nb[t] = (L[t] + kBlock - 1) / kBlock;
+    sum += nb[t];
+    most = max(most, nb[t]);
+    weights += pair_weight(L[t], p.mbps, kWaveSlices);
+  }
+  const int32_t all = wave_sum_i32(sum), longest = wave_max_i32(most);
+  // A pair of at most kPairShortBlocks blocks is not worth a cut (19 blocks: 6.8
+  // us by one workgroup, 8.3 by two); should no size fit, none is cut.
+  int32_t S = longest;
+  if (longest > kPairShortBlocks) {
+    // Lane i counts the units of its size: from an even share of the blocks up to
+    // three of them; the last one cuts nothing. (fp32 estimates; the exact count
+    // follows.)
+    const float share = (float)all / (float)p.units;
+    const int32_t size =
+        lane == kWave - 1
+            ? longest
+            : max(kUnitBlocksMin,
+                  ((int32_t)(share + share * lane * (1.f / 31.f)) / kPairWaves + 1) * kPairWaves);
+    const float per_block = 1.f / (float)size;
+    float count = 0.f;
+#pragma unroll
+    for (int t = 0; t < kUnitSets; ++t) {
+      const int32_t bits = __builtin_bit_cast(int32_t, (float)nb[t]);
+      count += (float)__popcll(__ballot(nb[t] > 0 && nb[t] <= kPairShortBlocks));
+      for (uint64_t rest = __ballot(nb[t] > kPairShortBlocks); rest; rest &= rest - 1) {
+        const int e = __ffsll((unsigned long long)rest) - 1;
+        count += ceilf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, e)) * per_block);
+      }
+    }
+    const uint64_t fit = __ballot(count <= (float)p.units) | (uint64_t)1 << (kWave - 1);
+    S = min(__builtin_amdgcn_readlane(size, __ffsll((unsigned long long)fit) - 1), longest);
+    const int32_t W = wave_sum_i32(weights) * p.hkv;
+    const float even = (float)all * (float)p.hkv / (float)p.cus;
+    if (uniform((float)S > even + lone_slack<G>(p, even, W, longest))) return kBadDivision;
+  }
+  int32_t units[kUnitSets], total;
+  for (;;) {
+    int32_t c = 0;
+#pragma unroll
+    for (int t = 0; t < kUnitSets; ++t) {
+      units[t] = nb[t] <= max(S, kPairShortBlocks) ? nb[t] > 0 : (nb[t] + S - 1) / S;
+      c += units[t];
+    }
+    total = wave_sum_i32(c);
+    if (total <= p.units) break;
+    S = longest;  // one unit a pair
+  }
+  if (v >= total) return kNoUnit;
+  int32_t before = 0;
+#pragma unroll
+  for (int t = 0; t < kUnitSets; ++t) {
+    const int32_t incl = before + wave_incl_scan_i32(units[t]);
+    const uint64_t hit = __ballot(v < incl && v >= incl - units[t]);
+    if (hit) {
+      const int e = __ffsll((unsigned long long)hit) - 1;
+      u.b = kWave * t + e;
+      u.L = __builtin_amdgcn_readlane(L[t], e);
+      u.units = __builtin_amdgcn_readlane(units[t], e);
+      u.unit0 = __builtin_amdgcn_readlane(incl, e) - u.units;
+    }
+    before = __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  const int32_t blocks = (u.L + kBlock - 1) / kBlock;
+  const int32_t part = u.units == 1 ? blocks : S;
+  u.first = (v - u.unit0) * part;
+  u.blocks = min(part, blocks - u.first);
+  return kUnitFound;
+}
+
+// Wavefront w of a unit takes its tiles w, w + kPairWaves, ...
+template <class F, int G>
+__device__ inline void unit_driver(const DecodeParams& p) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = uniform(threadIdx.x >> 6);
+  const int32_t g = blockIdx.x, v = blockIdx.y;
+  int32_t raw[kUnitSets];
+  load_lens<kUnitSets>(p, lane, raw);
+  const int32_t own = v < p.batch ? p.lens[v] : 1;
+  Unit u;
+  const UnitFound found = find_unit<G>(p, v, u, lane, raw);
+  if (found == kBadDivision) {
+    __shared__ GroupMerge<G> gm;
+    const int32_t index = v * p.hkv + g;
+    const int32_t workgroups = (p.max_slices + kWavesPerGroup - 1) / kWavesPerGroup;
+    if (index >= workgroups || wv >= kWavesPerGroup) return;
+    int32_t len0;
+    const SliceInfo si = plan_wave_slice<kFused>(p, index, &len0);
+    decode_driver<F, G, 1, kFused>(p, gm, index, workgroups, si, len0);
+    return;
+  }
+  if (own <= 0) zero_pair<G>(p, v, g);  // the grid has a workgroup per pair
+  if (found == kNoUnit) return;
+  auto block_of = [&](int32_t i) -> int32_t { return u.first + wv + kPairWaves * i; };
+  const int32_t ids = p.table[(size_t)u.b * p.mbps + min(block_of(lane), p.mbps - 1)];
+  typename F::Q q;
+  F::load_q(q, p.q + ((size_t)u.b * p.hq + g * G) * kHeadDim, lane);
+  const int32_t n = max(0, (u.blocks - wv + kPairWaves - 1) / kPairWaves);
+  pair_body<F, G>(p, u.b, g, u.L, n, min(kPairWaves, u.blocks), ids, q, block_of, u.units,
+                  v * p.hkv + g, [&](int32_t i) { return (u.unit0 + i) * p.hkv + g; }, lane, wv);
+}
+
+// kWhole: one workgroup per pair, longest first where they run in two rounds,
+// so that short ones fill the ends (index order / longest first: 64 requests of
+// U[512, 2048] tokens, 8 kv heads 57.7 / 55.9 us, 40 of them 41.3 / 35.9).
+constexpr int kLengthClasses = 16;
+constexpr int kWholeSets = kWholeMaxBatch / kWave;  // of 64 requests
+// Of kLoneBlocks, what remains where pairs follow each other on a compute unit:
+// a second start costs about 3 us (264 pairs of 32 blocks each, an even share of
+// 33: 21.8 us whole, 19.8 in wave slices).
+constexpr float kLoneBlocksTwoRounds = 12.f;
+
+// Rank r of the requests by length, longest first, to within a sixteenth of the
+// longest (ties in index order): a ballot for each of 16 classes, a scan over
+// the classes' counts. blocks: of request 64 wv + lane.
+__device__ inline int32_t request_of_rank(const DecodeParams& p, int32_t r, int32_t blocks,
+                                          int32_t longest, int lane, int wv) {
+  __shared__ uint64_t members[kLengthClasses * kWholeSets];  // [class][64 requests]
+  const int32_t groups = (p.batch + kWave - 1) / kWave;
+  if (wv < groups) {
+    const float per_width = 1.f / (float)(longest / kLengthClasses + 1);
+    const int32_t cls = wv * kWave + lane < p.batch
+                            ? max(0, kLengthClasses - 1 - (int32_t)((float)blocks * per_width))
+                            : -1;
+    uint64_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < kLengthClasses; ++k) {
+      const uint64_t m = __ballot(cls == k);
+      if (lane == k) mine = m;
+    }
+    if (lane < kLengthClasses) members[lane * groups + wv] = mine;
+  }
+  __syncthreads();
+  const int32_t entries = groups * kLengthClasses;
+  int32_t before = 0;
+  for (int32_t base = 0; base < entries; base += kWave) {
+    const uint64_t m = base + lane < entries ? members[base + lane] : 0;
+    const int32_t c = __popcll(m);
+    const int32_t incl = before + wave_incl_scan_i32(c);
+    const uint64_t hit = __ballot(incl > r);
+    if (hit) {
+      // The entry holding rank r, and in it the request with that many
+      // members below it.
+      const int e = __ffsll((unsigned long long)hit) - 1;
+      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m, e);
+      const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m >> 32), e);
+      const int32_t want =
+          r - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(c, e));
+      const int32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+      const bool member = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1;
+      const uint64_t at = __ballot(member && below == want);
+      return (base + e) % groups * kWave + __ffsll((unsigned long long)at) - 1;
+    }
+    before = __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  return 0;  // not reached: r is below the batch
+}
+
+template <class F, int G, bool kTwoRounds>
+__device__ inline void whole_driver(const DecodeParams& p) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = uniform(threadIdx.x >> 6);
+  const int32_t g = blockIdx.x, r = blockIdx.y;
+  auto block_of = [&](int32_t i) -> int32_t { return wv + kPairWaves * i; };
+  int32_t w[kPlanRegs] = {}, raw[kPlanRegs] = {};  // as plan_slice takes them
+  load_lens<kWholeSets>(p, lane, raw);
+  const int32_t index = r * p.hkv + g;  // of the workgroup, for wave slices
+  const int32_t wave = index * kWavesPerGroup + wv;
+  const int32_t len0 = p.lens[min(wave, p.batch - 1)];
+  // In one round pair (r, g) is this workgroup's, and its reads do not wait for
+  // the lengths.
+  int32_t b = min(r, p.batch - 1), ids = 0;
+  typename F::Q q;
+  if constexpr (!kTwoRounds) {
+    ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
+    F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
+  }
+  int32_t nb[kWholeSets], weights = 0, sum = 0, most = 0, own = 0;
+#pragma unroll
+  for (int t = 0; t < kWholeSets; ++t) {
+    raw[t] = kWave * t + lane < p.batch ? raw[t] : 0;
+    nb[t] = blocks_of(raw[t], p.mbps);
+    w[t] = pair_weight(raw[t], p.mbps, kWaveSlices);
+    weights += w[t];
+    sum += nb[t];
+    most = max(most, nb[t]);
+    if (t == wv) own = nb[t];
+  }
+  const int32_t W = wave_sum_i32(weights) * p.hkv;
+  const int32_t longest = wave_max_i32(most);
+  const float even = (float)wave_sum_i32(sum) * (float)p.hkv / (float)p.cus;
+  bool whole = (float)longest <= even + lone_slack<G>(p, even, W, longest);
+  if constexpr (kTwoRounds) {
+    // Two pairs of more than half of what a compute unit may have must not follow
+    // each other on one.
+    const float half = 0.5f * (even + kLoneBlocksOfEven * even + kLoneBlocksTwoRounds);
+    int32_t halves = 0;
+#pragma unroll
+    for (int t = 0; t < kWholeSets; ++t) halves += __popcll(__ballot((float)nb[t] > half));
+    whole = whole && halves * p.hkv <= p.cus;
+  }
+  if (uniform(whole)) {
+    if (r >= p.batch) return;
+    int32_t len;
+    if constexpr (kTwoRounds) {
+      // (Short pairs are not worth an order: 64 requests of U[50, 150] tokens 9.7
+      // us in index order, 11.7 longest first.)
+      if (longest > kPairShortBlocks)
+        b = uniform(request_of_rank(p, r, own, longest, lane, wv));
+      len = p.lens[b];
+      ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
+      F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
+    } else {
+      len = p.lens[b];
+    }
+    const int32_t L = clamp_len(uniform(len), p.mbps);
+    const int32_t blocks = (L + kBlock - 1) / kBlock;
+    if (blocks == 0) {
+      zero_pair<G>(p, b, g);
+      return;
+    }
+    const int32_t n = max(0, (blocks - wv + kPairWaves - 1) / kPairWaves);
+    pair_body<F, G>(p, b, g, L, n, min(kPairWaves, blocks), ids, q, block_of, 1, 0,
+                    [](int32_t) { return 0; }, lane, wv);
+    return;
+  }
+  const int32_t workgroups = (p.max_slices + kWavesPerGroup - 1) / kWavesPerGroup;
+  if (index >= workgroups || wv >= kWavesPerGroup) return;
+  __shared__ GroupMerge<G> gm;
+  const SliceInfo si = plan_slice<kWaveSlices>(p, wave, lane, W, w, raw);
+  decode_driver<F, G, 1, kFused>(p, gm, index, workgroups, si, len0);
 }
 
 }  // namespace neo

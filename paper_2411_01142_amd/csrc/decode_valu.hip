@@ -184,7 +184,10 @@ struct ValuFamily {
 
 template <int G, Schedule kSched>
 __global__ __launch_bounds__(kWave * kWavesPerGroup) void decode_valu_kernel(DecodeParams p) {
-  decode_driver<ValuFamily<G>, G, 1, kSched>(p);
+  __shared__ typename GroupMergeOf<G, kSched == kFused>::type gm;
+  int32_t len0;
+  const SliceInfo si = plan_wave_slice<kSched>(p, blockIdx.x, &len0);
+  decode_driver<ValuFamily<G>, G, 1, kSched>(p, gm, blockIdx.x, gridDim.x, si, len0);
 }
 
 template <int G>

@@ -46,11 +46,19 @@ constexpr int32_t kLongPairBlocks = 32;
 //  kPairs: no line and no slices; every (request, kv head) pair has the same
 //    number of workgroups (DecodeParams::parts), which take its chunks of
 //    kPairChunk blocks in turn.
-enum SliceMode { kWaveSlices = 0, kHeadSlices = 1, kPairs = 2 };
-constexpr int kPairWaves = 8;         // kPairs: wavefronts of a workgroup
+//  kUnits: every pair is cut into units of S blocks, one per workgroup, S chosen
+//    on the device from the lengths.
+//  kWhole: one workgroup per pair, longest first.
+//    (Both take wave slices instead where the lengths make them a bad division.)
+enum SliceMode { kWaveSlices = 0, kHeadSlices = 1, kPairs = 2, kUnits = 3, kWhole = 4 };
+constexpr bool has_plan(SliceMode mode) { return mode == kWaveSlices || mode == kHeadSlices; }
+constexpr int kPairWaves = 8;         // kPairs, kUnits, kWhole: wavefronts of a workgroup
 constexpr int kPairTilesPerWave = 2;  // of a chunk
 constexpr int kPairChunk = kPairWaves * kPairTilesPerWave;
-constexpr int kMaxOrderedBatch = 1024;
+constexpr int32_t kPairShortBlocks = 32;
+constexpr int32_t kUnitBlocksMin = 16;
+constexpr int32_t kUnitMaxBatch = 2 * kWave;   // lengths a kUnits workgroup reads
+constexpr int32_t kWholeMaxBatch = 8 * kWave;  // and a kWhole one
 constexpr int kHeadsPerSlice = 4;  // kHeadSlices: kv heads of a pair, one per wavefront
 // Head slices stream across pair ends, which costs a pair little more than its
 // arithmetic.
@@ -237,7 +245,9 @@ struct DecodeParams {
   int32_t slice_quantum;          // compute units x wavefronts per workgroup
   int32_t xcd8;                   // the device has eight XCDs (slice weights)
   int32_t parts;              // kPairs: workgroups of a pair
-  int32_t longest_first;      // kPairs: order of the requests (batch <= kMaxOrderedBatch)
+  int32_t units;              // kUnits: the most of a kv head, at least the batch
+  int32_t grid_y;             // kUnits, kWhole: workgroups per kv head
+  int32_t cus;                // compute units
   float scale_log2;           // scale * log2(e)
   int64_t blk_stride;         // elements from one block of a cache to the next (K and V alike)
 };

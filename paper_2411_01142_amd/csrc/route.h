@@ -1,0 +1,93 @@
+// How a decode call is divided: SliceMode and its parameters, from what the
+// host knows: the batch, the heads, the table's width (mbps) and the compute
+// units. The width bounds the lengths and says little else about them (a table
+// is as wide as a program's longest context), so it is used only where it makes
+// every batch of that width a good one for the division; what depends on the
+// lengths is decided on the device. A caller's slice cap is a cap on wavefronts'
+// slices.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "neo_internal.h"
+
+namespace neo {
+
+struct Route {
+  SliceMode mode;
+  int32_t parts;   // kPairs
+  int32_t units;   // kUnits
+  int32_t grid_y;  // kUnits, kWhole
+};
+
+// Times below: device time of a call with 32 / 8 heads on 256 compute units,
+// tables as wide as the longest request where no width is given.
+//
+// Without slices: up to two (request, kv head) pairs per compute unit. With more
+// of them short pairs lose (in planned slices / one workgroup per pair: 64
+// requests of U[50, 150] tokens, two pairs per compute unit, 13.3 / 9.6 us; 128,
+// four, 16.6 / 17.0), and beyond 32 blocks, where the device has to choose, the
+// gains and losses are alike (128 of U[500, 3000] 146 / 140, of U[100, 1000] 53.9
+// / 55.5, of 500 tokens 47.4 / 50.3).
+constexpr int32_t kPairsPerCu = 2;
+// A pair of at most kPairShortBlocks blocks is not worth a merge (19 blocks: 6.8
+// us by one workgroup, 8.3 by two), and any batch of such pairs is a good one.
+// kPairs beyond that: one request, whose pairs are equal, at any width; and
+// while a workgroup has at most as many blocks of the longest pair there may
+// be. Then the lengths are not worth a round trip (5 requests of U[50, 150]
+// tokens: 4.9 us so, 5.7 in units; 13 of U[100, 1500], at most 47 blocks: 13.2
+// so, 12.4 in units). Where pairs outnumber half of the compute units none is
+// cut, and a lone one of twice as many costs less than the round trip (32 of
+// U[50, 150], 64 columns: 6.0 so, 6.6 as kWhole).
+//
+// Cutting needs compute units to spare: up to half of them taken, units of at
+// most twice an even share of the blocks are enough (kUnits). With more pairs
+// none is cut (kWhole).
+//
+// (Tables of 500 columns, planned / here: 13 requests of U[100, 1500] 15.9 /
+// 12.5; 32 of 500 tokens 15.7 / 13.6; 64 of U[512, 2048], 2048 columns, 58.2 /
+// 52.4.)
+constexpr int32_t kMaxCus = 256;
+static_assert(kPairsPerCu * kMaxCus <= kWholeMaxBatch && kMaxCus / 2 <= kUnitMaxBatch,
+              "the kernels read that many lengths");
+
+// Head slices need whole groups of four kv heads, and pay once every compute
+// unit has a few (request, four heads) pairs with some blocks to stream: below
+// that a slice is a part of one or two pairs and the cut pairs' partials all
+// cross workgroups, where wave slices merge most of them in LDS. Measured, wave
+// / head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512,
+// 2048] tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512
+// of U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50,
+// 200] tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52
+// blocks) 53.9 / 54.0.
+constexpr int32_t kHeadPairsPerCu = 2;
+constexpr int32_t kHeadBlocksPerCu = 64;
+
+inline Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int32_t mbps,
+                   int32_t cus) {
+  if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {kWaveSlices, 0, 0, 0};
+  const int64_t pairs = (int64_t)batch * hkv;
+  if (pairs <= (int64_t)kPairsPerCu * cus && cus <= kMaxCus) {
+    const int32_t n = (int32_t)pairs;
+    const bool uncut = n > cus / 2;
+    if (mbps <= kPairShortBlocks || (uncut && n <= cus && mbps <= 2 * kPairShortBlocks))
+      return {kPairs, 1, 0, 0};
+    // (With a workgroup for every slice, should the device choose wave slices.)
+    const int32_t whole = (cus - 1) / hkv + 1;
+    if (uncut) return {kWhole, 0, 0, std::max(batch, whole)};
+    const int32_t parts = std::min(cus / n, (mbps - 1) / kPairChunk + 1);
+    if (batch == 1 || mbps <= kPairShortBlocks * parts) return {kPairs, parts, 0, 0};
+    return {kUnits, 0, cus / hkv, whole};
+  }
+  if (hkv % kHeadsPerSlice == 0) {
+    const int64_t groups = pairs / kHeadsPerSlice;
+    if (groups >= (int64_t)kHeadPairsPerCu * cus &&
+        groups * mbps >= (int64_t)kHeadBlocksPerCu * cus)
+      return {kHeadSlices, 0, 0, 0};
+  }
+  return {kWaveSlices, 0, 0, 0};
+}
+
+}  // namespace neo

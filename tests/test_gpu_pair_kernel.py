@@ -1,9 +1,13 @@
 """Decode attention of small batches, divided without a plan: every (request, kv
-head) pair goes to one workgroup or to a fixed number of them. At the edges of
-that division (no tokens, one tile, chunks of 16 blocks and their remainders,
-fewer chunks than workgroups, more chunks than workgroups, lengths far below
-the table's width, batches whose requests are taken longest first), for every query group, against the oracle, across launch
-schedules and entry points, and call after call on one workspace."""
+head) pair goes to one workgroup, to a fixed number of them, or is cut into
+units whose size comes from the lengths; where the lengths are bad for that, the
+call takes wave slices. At the edges of those divisions (no tokens, one tile,
+chunks of 16 blocks and their remainders, fewer chunks than workgroups, more
+chunks than workgroups, partials of more workgroups than a wavefront has lanes,
+lengths far below the table's width, batches whose requests are taken longest
+first, lengths just inside and far outside of what suits the division), for
+every query group, against the oracle, across launch schedules and entry points,
+and call after call on one workspace."""
 import ctypes
 
 import numpy as np
@@ -48,6 +52,27 @@ CASES = {
     "ordered_one_long": (2, [90] * 150 + [4000] + [0] * 20, 0),
     "ordered_rounds": (8, [(i * 353) % 2049 for i in range(180)], 0),
     "ordered_many_groups": (1, [(i * 7919) % 1000 for i in range(1000)], 1),
+    # a pair's partials from more than 64 workgroups
+    "pairs_196_workgroups": (1, [50021], 0),
+    "pairs_128_workgroups": (2, [40000], 0),
+    # units
+    "units_of_16_blocks": (8, [1, 16, 0, 500, 512, 513, 528, 900, 17, 0, 40, 0], 300),
+    "units_one_long": (1, [30000] + [200] * 40 + [0, 1, 512, 513], 0),
+    "units_two_long": (1, [50021, 40000, 5], 0),
+    "units_65_to_128_requests": (1, [(i * 353) % 2049 for i in range(128)], 100),
+    "units_three_heads": (3, [(i * 977) % 3000 for i in range(40)], 0),
+    "units_none": (8, [0] * 12, 200),
+    "units_bad": (1, [6400] * 86, 0),
+    # one workgroup a pair, in one round and in two
+    "whole": (8, [(i * 353) % 1700 + 300 for i in range(30)] + [0, 1], 0),
+    "whole_more_slices_than_pairs": (5, [1000 + 16 * i for i in range(30)], 0),
+    "whole_bad": (8, [4096] + [150] * 29, 0),
+    "whole_rounds": (8, [(i * 353) % 1537 + 512 for i in range(62)] + [0, 0], 200),
+    "whole_rounds_512": (1, [(i * 353) % 3840 + 256 for i in range(510)] + [0, 1], 0),
+    "whole_rounds_short": (4, [(i * 37) % 500 for i in range(100)], 50),
+    "whole_rounds_bad": (8, [4096] + [150] * 61 + [0, 1], 0),
+    "whole_rounds_halves": (8, [2048] * 33, 0),
+    "whole_rounds_none": (8, [0] * 40, 60),
 }
 
 
@@ -59,6 +84,10 @@ def test_pair_kernel_matches_the_oracle(name, group):
                         extra_table_cols=extra)
     print(f"[pairs] {name} G={group} Hkv={hkv} B={case.batch} mbps={case.max_blocks_per_seq}",
           flush=True)
+    want = name.split("_")[0]
+    if want in ("pairs", "units", "whole"):
+        assert neo.debug_division(case.batch, case.num_q_heads, case.num_kv_heads,
+                                  case.max_blocks_per_seq) == want
     q, k, v, bt, sl = case.to_torch("cuda", kv_layout="interleaved")
     ws = neo.new_workspace(case.batch, case.num_q_heads, case.num_kv_heads)
 
