@@ -287,24 +287,36 @@ __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_pair_kernel(
   pair_driver<MfmaFamily<G>, G>(p);
 }
 
-template <int G>
+template <int G, int kSets>
 __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_unit_kernel(
     const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
   p.lens = lens;
   p.batch = batch;
   p.hkv = hkv;
   p.mbps = mbps;
-  unit_driver<MfmaFamily<G>, G>(p);
+  unit_driver<MfmaFamily<G>, G, kSets>(p);
 }
 
-template <int G, bool kTwoRounds>
+template <int G, bool kTwoRounds, int kSets>
 __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_whole_kernel(
     const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
   p.lens = lens;
   p.batch = batch;
   p.hkv = hkv;
   p.mbps = mbps;
-  whole_driver<MfmaFamily<G>, G, kTwoRounds>(p);
+  whole_driver<MfmaFamily<G>, G, kTwoRounds, kSets>(p);
+}
+
+template <int G, int kSets>
+hipError_t launch_whole(const DecodeParams& p, hipStream_t stream) {
+  const dim3 grid(p.hkv, p.grid_y), block(kWave * kPairWaves);
+  if ((int64_t)p.batch * p.hkv > p.cus)
+    decode_whole_kernel<G, true, kSets>
+        <<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+  else
+    decode_whole_kernel<G, false, kSets>
+        <<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+  return hipGetLastError();
 }
 
 template <int G, SliceMode kMode>
@@ -333,17 +345,17 @@ hipError_t launch_mode(const DecodeParams& p, SliceMode mode, Schedule sched, in
     return hipGetLastError();
   }
   if (mode == kUnits) {
-    decode_unit_kernel<G><<<dim3(p.hkv, p.grid_y), kWave * kPairWaves, 0, stream>>>(
-        p.lens, p.batch, p.hkv, p.mbps, p);
+    const dim3 grid(p.hkv, p.grid_y), block(kWave * kPairWaves);
+    if (p.batch <= kWave)
+      decode_unit_kernel<G, 1><<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
+    else
+      decode_unit_kernel<G, kUnitMaxBatch / kWave>
+          <<<grid, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
     return hipGetLastError();
   }
   if (mode == kWhole) {
-    const dim3 grid2(p.hkv, p.grid_y), block(kWave * kPairWaves);
-    if ((int64_t)p.batch * p.hkv > p.cus)
-      decode_whole_kernel<G, true><<<grid2, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
-    else
-      decode_whole_kernel<G, false><<<grid2, block, 0, stream>>>(p.lens, p.batch, p.hkv, p.mbps, p);
-    return hipGetLastError();
+    return p.batch <= kWave ? launch_whole<G, 1>(p, stream)
+                            : launch_whole<G, kWholeSets>(p, stream);
   }
   return mode == kHeadSlices ? launch_g<G, kHeadSlices>(p, sched, grid, stream)
                              : launch_g<G, kWaveSlices>(p, sched, grid, stream);

@@ -31,14 +31,14 @@
 //  kPairs: one request of 877 tokens 12.8 -> 7.8 us, of 50021 59 -> 36; 4
 //    requests of U[64, 512] with 32 / 32 heads 9.6 -> 8.1; 64 of U[50, 150]
 //    13.3 -> 9.6.
-//  kUnits, tables of 500 blocks: 13 requests of U[100, 1500] 15.9 -> 12.5, 5 of
-//    U[50, 150] 8.8 -> 5.7, 5 of 8000 tokens 37.4 -> 30.5, one of 8000 among 12
-//    of U[75, 150] 31.4 -> 13.6. (Two fixed workgroups a pair: 14.8, 4.9, 30.2
-//    and 24.0.)
-//  kWhole: 64 of U[512, 2048] 58 -> 52, 64 of 2048 tokens 88.5 -> 84, 32 of
-//    U[100, 1000] 19.7 -> 16.2; 512 of U[256, 4096] with 8 / 1 heads 102 -> 90.
-//    Where it takes wave slices: one of 4096 among 64 of U[75, 150] 20.6 -> 21.1
-//    (whole pairs 41.6), 64 lognormal around 500 34.0 -> 34.5 (44.2).
+//  kUnits, tables of 500 blocks: 13 requests of U[100, 1500] 15.9 -> 12.3, 5 of
+//    U[50, 150] 8.8 -> 5.6, 5 of 8000 tokens 37.0 -> 30.2, one of 8000 among 12
+//    of U[75, 150] 31.3 -> 13.6. (Fixed workgroups for every pair: 14.9, 4.9,
+//    30.5 and 23.9.)
+//  kWhole: 64 of U[512, 2048] 58 -> 51, 64 of 2048 tokens 89 -> 82, 32 of
+//    U[100, 1000] 19.7 -> 15.5; 512 of U[256, 4096] with 8 / 1 heads 102 -> 90.
+//    Where it takes wave slices: one of 4096 among 64 of U[75, 150] 20.7 -> 20.7
+//    (whole pairs 41.6), 64 lognormal around 500 33.9 -> 33.8 (44.2).
 #pragma once
 
 #include "decode_common.h"
@@ -239,9 +239,10 @@ __device__ inline float lone_slack(const DecodeParams& p, float even, int32_t W,
          kLoneBlocksPerRow * G * (float)longest * slices / (float)max(W, 1);
 }
 
-// Lengths of the first 64 kSets requests, 64 t + lane in raw[t] (0 past the
-// batch): straight-line code, since a branch would make the compiler wait for
-// what is requested after them.
+// Lengths of the first 64 kSets requests, 64 t + lane in raw[t] (past the batch
+// the last one's): straight-line code, since a branch would make the compiler
+// wait for what is requested after them. Few sets are worth kernels of their own:
+// with room for 512 requests, 64 of U[512, 2048] tokens take 52 us instead of 50.5.
 template <int kSets>
 __device__ inline void load_lens(const DecodeParams& p, int lane, int32_t* raw) {
 #pragma unroll
@@ -262,14 +263,13 @@ enum UnitFound { kUnitFound, kNoUnit, kBadDivision };
 // Unit v. S is the smallest of 64 sizes that gives at most p.units units (the
 // grid has one for every request). Every wavefront finds S and the unit by
 // itself from all lengths.
-constexpr int kUnitSets = kUnitMaxBatch / kWave;
-template <int G>
+template <int G, int kSets>
 __device__ inline UnitFound find_unit(const DecodeParams& p, int32_t v, Unit& u, int lane,
                                       const int32_t* raw) {
-  int32_t L[kUnitSets], nb[kUnitSets];
+  int32_t L[kSets], nb[kSets];
   int32_t sum = 0, most = 0, weights = 0;
 #pragma unroll
-  for (int t = 0; t < kUnitSets; ++t) {
+  for (int t = 0; t < kSets; ++t) {
     L[t] = kWave * t + lane < p.batch ? clamp_len(raw[t], p.mbps) : 0;
     nb[t] = (L[t] + kBlock - 1) / kBlock;
     sum += nb[t];
@@ -281,37 +281,34 @@ __device__ inline UnitFound find_unit(const DecodeParams& p, int32_t v, Unit& u,
   // us by one workgroup, 8.3 by two); should no size fit, none is cut.
   int32_t S = longest;
   if (longest > kPairShortBlocks) {
-    // Lane i counts the units of its size: from an even share of the blocks up to
-    // three of them; the last one cuts nothing. (fp32 estimates; the exact count
-    // follows.)
+    // Sizes from an even share of the blocks up to three of them; number 63 cuts
+    // nothing. (The counts are fp32 estimates; the exact one follows.)
     const float share = (float)all / (float)p.units;
-    const int32_t size =
-        lane == kWave - 1
-            ? longest
-            : max(kUnitBlocksMin,
-                  ((int32_t)(share + share * lane * (1.f / 31.f)) / kPairWaves + 1) * kPairWaves);
-    const float per_block = 1.f / (float)size;
-    float count = 0.f;
+    auto size_of = [&](int32_t i) -> int32_t {
+      const int32_t blocks = (int32_t)(share + share * (float)i * (1.f / 31.f));
+      return max(kUnitBlocksMin, (blocks / kPairWaves + 1) * kPairWaves);
+    };
+    int32_t i = 0;
 #pragma unroll
-    for (int t = 0; t < kUnitSets; ++t) {
-      const int32_t bits = __builtin_bit_cast(int32_t, (float)nb[t]);
-      count += (float)__popcll(__ballot(nb[t] > 0 && nb[t] <= kPairShortBlocks));
-      for (uint64_t rest = __ballot(nb[t] > kPairShortBlocks); rest; rest &= rest - 1) {
-        const int e = __ffsll((unsigned long long)rest) - 1;
-        count += ceilf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(bits, e)) * per_block);
-      }
+    for (int32_t step = 32; step > 0; step /= 2) {
+      const float per_block = __builtin_amdgcn_rcpf((float)size_of(i + step - 1));
+      int32_t count = 0;
+#pragma unroll
+      for (int t = 0; t < kSets; ++t)
+        count += nb[t] <= kPairShortBlocks ? nb[t] > 0 : (int32_t)ceilf((float)nb[t] * per_block);
+      if (wave_sum_i32(count) > p.units) i += step;
     }
-    const uint64_t fit = __ballot(count <= (float)p.units) | (uint64_t)1 << (kWave - 1);
-    S = min(__builtin_amdgcn_readlane(size, __ffsll((unsigned long long)fit) - 1), longest);
+    S = i < 63 ? min(size_of(i), longest) : longest;
+    S = uniform(S);
     const int32_t W = wave_sum_i32(weights) * p.hkv;
     const float even = (float)all * (float)p.hkv / (float)p.cus;
     if (uniform((float)S > even + lone_slack<G>(p, even, W, longest))) return kBadDivision;
   }
-  int32_t units[kUnitSets], total;
+  int32_t units[kSets], total;
   for (;;) {
     int32_t c = 0;
 #pragma unroll
-    for (int t = 0; t < kUnitSets; ++t) {
+    for (int t = 0; t < kSets; ++t) {
       units[t] = nb[t] <= max(S, kPairShortBlocks) ? nb[t] > 0 : (nb[t] + S - 1) / S;
       c += units[t];
     }
@@ -322,7 +319,7 @@ __device__ inline UnitFound find_unit(const DecodeParams& p, int32_t v, Unit& u,
   if (v >= total) return kNoUnit;
   int32_t before = 0;
 #pragma unroll
-  for (int t = 0; t < kUnitSets; ++t) {
+  for (int t = 0; t < kSets; ++t) {
     const int32_t incl = before + wave_incl_scan_i32(units[t]);
     const uint64_t hit = __ballot(v < incl && v >= incl - units[t]);
     if (hit) {
@@ -342,16 +339,16 @@ __device__ inline UnitFound find_unit(const DecodeParams& p, int32_t v, Unit& u,
 }
 
 // Wavefront w of a unit takes its tiles w, w + kPairWaves, ...
-template <class F, int G>
+template <class F, int G, int kSets>
 __device__ inline void unit_driver(const DecodeParams& p) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = uniform(threadIdx.x >> 6);
   const int32_t g = blockIdx.x, v = blockIdx.y;
-  int32_t raw[kUnitSets];
-  load_lens<kUnitSets>(p, lane, raw);
+  int32_t raw[kSets];
+  load_lens<kSets>(p, lane, raw);
   const int32_t own = v < p.batch ? p.lens[v] : 1;
   Unit u;
-  const UnitFound found = find_unit<G>(p, v, u, lane, raw);
+  const UnitFound found = find_unit<G, kSets>(p, v, u, lane, raw);
   if (found == kBadDivision) {
     __shared__ GroupMerge<G> gm;
     const int32_t index = v * p.hkv + g;
@@ -380,63 +377,72 @@ constexpr int kLengthClasses = 16;
 constexpr int kWholeSets = kWholeMaxBatch / kWave;  // of 64 requests
 // Of kLoneBlocks, what remains where pairs follow each other on a compute unit:
 // a second start costs about 3 us (264 pairs of 32 blocks each, an even share of
-// 33: 21.8 us whole, 19.8 in wave slices).
+// 33: 21.8 us whole, 19.4 in wave slices).
 constexpr float kLoneBlocksTwoRounds = 12.f;
 
-// Rank r of the requests by length, longest first, to within a sixteenth of the
-// longest (ties in index order): a ballot for each of 16 classes, a scan over
-// the classes' counts. blocks: of request 64 wv + lane.
+// The request of rank r, longest first to within a sixteenth of the longest
+// (ties in index order): a ballot for each of 16 classes, a scan over the
+// classes' counts. blocks: of request 64 wv + lane, or with up to 64 requests
+// (kOneSet) of request lane, when no wavefront needs another's ballots.
+template <bool kOneSet>
 __device__ inline int32_t request_of_rank(const DecodeParams& p, int32_t r, int32_t blocks,
                                           int32_t longest, int lane, int wv) {
-  __shared__ uint64_t members[kLengthClasses * kWholeSets];  // [class][64 requests]
-  const int32_t groups = (p.batch + kWave - 1) / kWave;
-  if (wv < groups) {
+  const int32_t groups = kOneSet ? 1 : (p.batch + kWave - 1) / kWave;
+  const int32_t gr = kOneSet ? 0 : wv;
+  uint64_t mine = 0;  // lane k: the members of class k
+  if (gr < groups) {
     const float per_width = 1.f / (float)(longest / kLengthClasses + 1);
-    const int32_t cls = wv * kWave + lane < p.batch
+    const int32_t cls = gr * kWave + lane < p.batch
                             ? max(0, kLengthClasses - 1 - (int32_t)((float)blocks * per_width))
                             : -1;
-    uint64_t mine = 0;
 #pragma unroll
     for (int k = 0; k < kLengthClasses; ++k) {
       const uint64_t m = __ballot(cls == k);
       if (lane == k) mine = m;
     }
-    if (lane < kLengthClasses) members[lane * groups + wv] = mine;
   }
-  __syncthreads();
-  const int32_t entries = groups * kLengthClasses;
-  int32_t before = 0;
-  for (int32_t base = 0; base < entries; base += kWave) {
-    const uint64_t m = base + lane < entries ? members[base + lane] : 0;
+  // Entries of 64 requests in the order of their classes; in the one holding
+  // rank r, the request with that many members below it.
+  auto find = [&](uint64_t m, int32_t before, int32_t* past) -> int32_t {
     const int32_t c = __popcll(m);
     const int32_t incl = before + wave_incl_scan_i32(c);
+    *past = __builtin_amdgcn_readlane(incl, kWave - 1);
     const uint64_t hit = __ballot(incl > r);
-    if (hit) {
-      // The entry holding rank r, and in it the request with that many
-      // members below it.
-      const int e = __ffsll((unsigned long long)hit) - 1;
-      const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m, e);
-      const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m >> 32), e);
-      const int32_t want =
-          r - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(c, e));
-      const int32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-      const bool member = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1;
-      const uint64_t at = __ballot(member && below == want);
-      return (base + e) % groups * kWave + __ffsll((unsigned long long)at) - 1;
+    if (!hit) return -1;
+    const int e = __ffsll((unsigned long long)hit) - 1;
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)m, e);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(m >> 32), e);
+    const int32_t want =
+        r - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(c, e));
+    const int32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    const bool member = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1;
+    const uint64_t at = __ballot(member && below == want);
+    return e * kWave + __ffsll((unsigned long long)at) - 1;
+  };
+  int32_t before = 0;
+  if constexpr (kOneSet) {
+    return max(0, find(mine, 0, &before)) % kWave;
+  } else {
+    __shared__ uint64_t members[kLengthClasses * kWholeSets];  // [class][64 requests]
+    if (gr < groups && lane < kLengthClasses) members[lane * groups + gr] = mine;
+    __syncthreads();
+    const int32_t entries = groups * kLengthClasses;
+    for (int32_t base = 0; base < entries; base += kWave) {
+      const int32_t at = find(base + lane < entries ? members[base + lane] : 0, before, &before);
+      if (at >= 0) return (base + at / kWave) % groups * kWave + at % kWave;
     }
-    before = __builtin_amdgcn_readlane(incl, kWave - 1);
+    return 0;  // not reached: r is below the batch
   }
-  return 0;  // not reached: r is below the batch
 }
 
-template <class F, int G, bool kTwoRounds>
+template <class F, int G, bool kTwoRounds, int kSets>
 __device__ inline void whole_driver(const DecodeParams& p) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = uniform(threadIdx.x >> 6);
   const int32_t g = blockIdx.x, r = blockIdx.y;
   auto block_of = [&](int32_t i) -> int32_t { return wv + kPairWaves * i; };
   int32_t w[kPlanRegs] = {}, raw[kPlanRegs] = {};  // as plan_slice takes them
-  load_lens<kWholeSets>(p, lane, raw);
+  load_lens<kSets>(p, lane, raw);
   const int32_t index = r * p.hkv + g;  // of the workgroup, for wave slices
   const int32_t wave = index * kWavesPerGroup + wv;
   const int32_t len0 = p.lens[min(wave, p.batch - 1)];
@@ -448,16 +454,16 @@ __device__ inline void whole_driver(const DecodeParams& p) {
     ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
     F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
   }
-  int32_t nb[kWholeSets], weights = 0, sum = 0, most = 0, own = 0;
+  int32_t nb[kSets], weights = 0, sum = 0, most = 0, own = 0;
 #pragma unroll
-  for (int t = 0; t < kWholeSets; ++t) {
+  for (int t = 0; t < kSets; ++t) {
     raw[t] = kWave * t + lane < p.batch ? raw[t] : 0;
     nb[t] = blocks_of(raw[t], p.mbps);
     w[t] = pair_weight(raw[t], p.mbps, kWaveSlices);
     weights += w[t];
     sum += nb[t];
     most = max(most, nb[t]);
-    if (t == wv) own = nb[t];
+    if (kSets == 1 || t == wv) own = nb[t];
   }
   const int32_t W = wave_sum_i32(weights) * p.hkv;
   const int32_t longest = wave_max_i32(most);
@@ -469,7 +475,7 @@ __device__ inline void whole_driver(const DecodeParams& p) {
     const float half = 0.5f * (even + kLoneBlocksOfEven * even + kLoneBlocksTwoRounds);
     int32_t halves = 0;
 #pragma unroll
-    for (int t = 0; t < kWholeSets; ++t) halves += __popcll(__ballot((float)nb[t] > half));
+    for (int t = 0; t < kSets; ++t) halves += __popcll(__ballot((float)nb[t] > half));
     whole = whole && halves * p.hkv <= p.cus;
   }
   if (uniform(whole)) {
@@ -479,7 +485,7 @@ __device__ inline void whole_driver(const DecodeParams& p) {
       // (Short pairs are not worth an order: 64 requests of U[50, 150] tokens 9.7
       // us in index order, 11.7 longest first.)
       if (longest > kPairShortBlocks)
-        b = uniform(request_of_rank(p, r, own, longest, lane, wv));
+        b = uniform(request_of_rank<kSets == 1>(p, r, own, longest, lane, wv));
       len = p.lens[b];
       ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
       F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);

@@ -28,27 +28,24 @@ struct Route {
 // Without slices: up to two (request, kv head) pairs per compute unit. With more
 // of them short pairs lose (in planned slices / one workgroup per pair: 64
 // requests of U[50, 150] tokens, two pairs per compute unit, 13.3 / 9.6 us; 128,
-// four, 16.6 / 17.0), and beyond 32 blocks, where the device has to choose, the
-// gains and losses are alike (128 of U[500, 3000] 146 / 140, of U[100, 1000] 53.9
-// / 55.5, of 500 tokens 47.4 / 50.3).
+// four, 16.6 / 17.0, and 18.3 in tables of 200 columns, where the device has to
+// choose). Long ones would gain (128 of U[500, 3000] 147 / 138, of 500 tokens 47.4
+// / 48.1; 512 requests of two kv heads 155 / 150 and 50.5 / 55.0).
 constexpr int32_t kPairsPerCu = 2;
 // A pair of at most kPairShortBlocks blocks is not worth a merge (19 blocks: 6.8
 // us by one workgroup, 8.3 by two), and any batch of such pairs is a good one.
 // kPairs beyond that: one request, whose pairs are equal, at any width; and
 // while a workgroup has at most as many blocks of the longest pair there may
 // be. Then the lengths are not worth a round trip (5 requests of U[50, 150]
-// tokens: 4.9 us so, 5.7 in units; 13 of U[100, 1500], at most 47 blocks: 13.2
-// so, 12.4 in units). Where pairs outnumber half of the compute units none is
+// tokens: 4.9 us so, 5.6 in units; 13 of U[100, 1500], at most 47 blocks: 13.2
+// so, 12.3 in units). Where pairs outnumber half of the compute units none is
 // cut, and a lone one of twice as many costs less than the round trip (32 of
-// U[50, 150], 64 columns: 6.0 so, 6.6 as kWhole).
+// U[50, 150]: 6.0 so, 5.9-6.6 as kWhole).
 //
 // Cutting needs compute units to spare: up to half of them taken, units of at
 // most twice an even share of the blocks are enough (kUnits). With more pairs
 // none is cut (kWhole).
 //
-// (Tables of 500 columns, planned / here: 13 requests of U[100, 1500] 15.9 /
-// 12.5; 32 of 500 tokens 15.7 / 13.6; 64 of U[512, 2048], 2048 columns, 58.2 /
-// 52.4.)
 constexpr int32_t kMaxCus = 256;
 static_assert(kPairsPerCu * kMaxCus <= kWholeMaxBatch && kMaxCus / 2 <= kUnitMaxBatch,
               "the kernels read that many lengths");
