@@ -32,8 +32,13 @@ HIPCC_FLAGS = [
 # lengths pointer, batch, kv heads, table stride) arrive preloaded in SGPRs,
 # so each wave's first length read goes out without waiting for a
 # kernel-argument load.
+# A kernel that may use more than 256 registers keeps its matrix-core
+# accumulators in vector registers all the same: the softmax rescales them at
+# every step, and from accumulation registers each would be moved there and back
+# (722 moves in the group-4 head-slice kernel, 50 with this).
 HIPCC_SOURCE_FLAGS = {
-    "decode_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=4"],
+    "decode_mfma.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=4",
+                        "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

@@ -335,6 +335,7 @@ neo_status neo_decode_attention_events(const void* q, const void* k_cache, const
   p.units = r.units;
   p.grid_y = r.grid_y;
   p.cus = cus;
+  p.head_positions = neo::kHeadPositionsPerCu * cus;
   p.scale_log2 = scale * 1.4426950408889634f;
   p.blk_stride = kv_block_stride != 0 ? kv_block_stride : (int64_t)num_kv_heads * neo::kTileElems;
 
@@ -453,6 +454,7 @@ neo_status neo_decode_attention_noalloc(const void* q, const void* k_cache, cons
   p.units = r.units;
   p.grid_y = r.grid_y;
   p.cus = cus;
+  p.head_positions = neo::kHeadPositionsPerCu * cus;
   const hipError_t e = neo::launch_decode_mfma(p, group, r.mode, neo::kFused, grid, s);
   if (e != hipSuccess) return set_error(NEO_ERR_HIP, "decode launch: %s", hipGetErrorString(e));
   return ok();

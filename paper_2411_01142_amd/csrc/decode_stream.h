@@ -67,8 +67,22 @@ __device__ inline void stream_driver(const DecodeParams& p) {
   const int32_t len0 = wave < p.batch ? p.lens[wave] : 0;
   __shared__ float stash[kWavesPerGroup][(kStash + 1) * G * kHeadDim];
   __shared__ int32_t stash_row[kWavesPerGroup][kStash];  // first output row of each slot
-  const SliceInfo si =
-      kSched == kStaged ? read_plan<kMode>(p, slice) : plan_in_wave<kMode>(p, slice, lane);
+  int32_t w[kPlanRegs], raw[kPlanRegs];
+  const int32_t W = kSched == kStaged ? p.hdr->total : plan_total<kMode>(p, lane, w, raw);
+  if (W < p.head_positions) {
+    // Too little for head slices: wave slices, merged in this kernel under every
+    // schedule. (The two-kernel launch's combine reads the total alone then.)
+    if (kSched == kTwoKernel && wave == 0 && lane == 0) p.hdr->total = W;
+    static_assert(sizeof(GroupMerge<G>) <= sizeof(stash), "the merge state takes the stash's place");
+    // (Planned anew: reusing the lengths above keeps them in registers and costs
+    // the loop below 0.5 %.)
+    const SliceInfo si = plan_in_wave<kWaveSlices>(p, wave, lane);
+    decode_driver<F, G, 1, kFused>(p, *reinterpret_cast<GroupMerge<G>*>(&stash[0][0]), blockIdx.x,
+                                   gridDim.x, si, len0);
+    return;
+  }
+  const SliceInfo si = kSched == kStaged ? read_plan<kMode>(p, slice)
+                                         : plan_slice<kMode>(p, slice, lane, W, w, raw);
   zero_empty_rows(p, wave, gridDim.x * kWavesPerGroup, lane, len0);
   if (kSched == kTwoKernel && lane == 0 && wv == 0) record_plan<kMode>(p, si, slice);
   // The plan is the workgroup's: its wavefronts leave together, here and

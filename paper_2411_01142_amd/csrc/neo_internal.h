@@ -42,7 +42,8 @@ constexpr int32_t kLongPairBlocks = 32;
 // How the tiles are laid out on the weighted line and who runs a slice of it.
 //  kWaveSlices: a pair is (request, kv head); one slice per wavefront.
 //  kHeadSlices: a pair is (request, four kv heads); one slice per workgroup,
-//    whose four wavefronts walk the same blocks together, one head each.
+//    whose four wavefronts walk the same blocks together, one head each; wave
+//    slices instead where the lengths leave the line too short.
 //  kPairs: no line and no slices; every (request, kv head) pair has the same
 //    number of workgroups (DecodeParams::parts), which take its chunks of
 //    kPairChunk blocks in turn.
@@ -244,6 +245,7 @@ struct DecodeParams {
   int32_t max_slices, min_tiles;  // min_tiles == 0: the default slice policy
   int32_t slice_quantum;          // compute units x wavefronts per workgroup
   int32_t xcd8;                   // the device has eight XCDs (slice weights)
+  int32_t head_positions;         // kHeadSlices: with fewer, the call takes wave slices
   int32_t parts;              // kPairs: workgroups of a pair
   int32_t units;              // kUnits: the most of a kv head, at least the batch
   int32_t grid_y;             // kUnits, kWhole: workgroups per kv head

@@ -136,6 +136,7 @@ __global__ __launch_bounds__(kWave * kWavesPerGroup) void combine_kernel(DecodeP
   for (int h = 0; h < G; ++h)
     asm volatile("" ::"v"(la[h]), "v"(lb[h]), "v"(oa[h].x), "v"(oa[h].y), "v"(ob[h].x),
                  "v"(ob[h].y));
+  if (kMode == kHeadSlices && W < p.head_positions) return;  // merged by the decode kernel
   if (s >= n >> kShift) return;
   const int32_t cost = pair_cost(a.nb, kMode);
   if (a.x <= cost) return;                      // no tile of the pair before the boundary

@@ -54,13 +54,23 @@ static_assert(kPairsPerCu * kMaxCus <= kWholeMaxBatch && kMaxCus / 2 <= kUnitMax
 // unit has a few (request, four heads) pairs with some blocks to stream: below
 // that a slice is a part of one or two pairs and the cut pairs' partials all
 // cross workgroups, where wave slices merge most of them in LDS. Measured, wave
-// / head slices, 32 / 8 heads on 256 compute units: 128 requests of U[512,
-// 2048] tokens (one pair each) 107.6 / 109.4 us, 256 (two) 204.8 / 203.5, 512
-// of U[256, 4096] with 64 / 8 heads (four) 681 / 643; short requests of U[50,
-// 200] tokens, 256 (two pairs, 26 blocks at most) 29.9 / 32.2 us, 512 (52
-// blocks) 53.9 / 54.0.
+// / head slices: 128 requests of U[512, 2048] tokens (one pair each) 107.6 /
+// 109.4 us; with two, 256 of U[512, 2048] 204.8 / 203.5, of U[1000, 2000] 247.7 /
+// 246.6, of U[256, 4096] 350 / 341, lognormal 295.7 / 287.1 (dense caches 314.9
+// / 311.1); with four, 512 of U[256, 4096] 697 / 681 (64 / 8 heads 681 / 643).
+// How large the gain is depends on the card, whose XCDs are unlike: a lognormal
+// batch with two pairs each has also measured 288 / 296.
 constexpr int32_t kHeadPairsPerCu = 2;
-constexpr int32_t kHeadBlocksPerCu = 64;
+// The kernel takes wave slices when the batch has fewer positions than this per
+// compute unit (a pair of n blocks has n + 1). Wave slices / wave slices found
+// out on the device / head slices, by positions: 7 (256 requests of U[10, 60]
+// tokens) 16.0 / 17.3 / 19.2 us, 15 (512 of them) 24.7 / 25.9 / 27.6, 19 (256 of
+// U[50, 200]) 30.0 / 31.4 / 32.4, 28 (384) 42.1 / 43.3 / 42.6, 30 (1024 of U[10,
+// 60]) 44.9 / 46.3 / 45.0, 37 (512 of U[50, 200]) 54.1 / - / 53.3, 52 (256, four
+// of them of 16000 tokens) 79.7 / - / 75.6. The host takes wave slices at once
+// where the table has no room for more.
+constexpr int32_t kHeadPositionsPerCu = 24;
+constexpr int32_t kHeadWidthPerCu = 64;
 
 inline Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t hkv, int32_t mbps,
                    int32_t cus) {
@@ -81,7 +91,7 @@ inline Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t h
   if (hkv % kHeadsPerSlice == 0) {
     const int64_t groups = pairs / kHeadsPerSlice;
     if (groups >= (int64_t)kHeadPairsPerCu * cus &&
-        groups * mbps >= (int64_t)kHeadBlocksPerCu * cus)
+        groups * mbps >= (int64_t)kHeadWidthPerCu * cus)
       return {kHeadSlices, 0, 0, 0};
   }
   return {kWaveSlices, 0, 0, 0};
