@@ -109,7 +109,8 @@ constexpr int32_t kXcdWeightMinTiles = 16;
 constexpr int32_t kXcdEvenUnitsHeads = 33;
 constexpr int32_t kXcdPeriodUnits = 4 * (kXcdEvenUnits + kXcdOddUnits);  // 8 slices
 struct SliceGeom {
-  int32_t W, n;      // positions and slices, 0 < n <= min(W, NEO_MAX_SLICES) (n = 0: no slices)
+  int32_t W, n;      // positions and slices, 0 < n <= min(W, NEO_MAX_SLICES) (n = 0: no
+                     // slices; head slices: n = 4, one workgroup's, also for W < 4)
   int32_t weighted;  // 0, or the units of a slice on an even XCD
   int32_t cn;        // C(n)
   int32_t a, r;      // W = a C(n) + r

@@ -3,7 +3,8 @@ no 64-bit division) against its exact integer definition, on the host.
 
 The same header the kernels include is compiled host-only with hipcc; the
 program checks every slice boundary of several thousand (W, n) pairs, with and
-without the per-XCD slice weights."""
+without the per-XCD slice weights of either kind, and the workgroups' slices of
+head slices."""
 import os
 import subprocess
 
