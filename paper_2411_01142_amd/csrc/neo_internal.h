@@ -106,6 +106,8 @@ constexpr int32_t kXcdWeightMinTiles = 16;
 // ones on the 70B layer (mean end 652-667 against 614-643 us), with equal
 // slices 35 us before them, with 33 : 31 within 10 us: 672, 683 and 666 us a
 // call; skewed mix 270, 272, 264; lognormal mix over dense caches 298, 296, 293.
+// Cards differ: on another one equal slices are the best of the three (lognormal
+// mix 290, 283, 287 us; over dense caches 314, 305, 311).
 constexpr int32_t kXcdEvenUnitsHeads = 33;
 constexpr int32_t kXcdPeriodUnits = 4 * (kXcdEvenUnits + kXcdOddUnits);  // 8 slices
 struct SliceGeom {

@@ -1,6 +1,6 @@
 """Decode attention captured in a HIP graph (torch.cuda.CUDAGraph) and replayed:
 the allocation-free entry point and the workspace entry point, on interleaved
-caches. Between replays the query rows are rewritten in place and the program
+caches, in every division of a call. Between replays the query rows are rewritten in place and the program
 runs eager work of its own; every replay must give the bits the eager call
 gives on the same inputs, and match the oracle."""
 import ctypes
@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import paper_2411_01142_amd as neo
+from division_cases import DIVISION_CASES, division_case
 from paper_2411_01142_amd import workloads as W
 
 torch = pytest.importorskip("torch")
@@ -37,8 +38,18 @@ def _errors(y, r):
 
 @pytest.mark.parametrize("entry", ["noalloc", "workspace"])
 def test_graph_replays_match_eager_calls(entry):
-    lib = neo.load_library()
     case = W.build_case([900, 17, 3000, 1, 0, 2048, 64, 511, 1500, 33], 32, 8, 128, 16, seed=91)
+    check_replays(entry, case)
+
+
+@pytest.mark.parametrize("name", list(DIVISION_CASES))
+@pytest.mark.parametrize("entry", ["noalloc", "workspace"])
+def test_graph_replays_of_every_division(entry, name):
+    check_replays(entry, division_case(name))
+
+
+def check_replays(entry, case):
+    lib = neo.load_library()
     print(f"[graph] {entry}: B={case.batch} Hq={case.num_q_heads} Hkv={case.num_kv_heads}",
           flush=True)
     q, k, v, bt, sl = case.to_torch("cuda", kv_layout="interleaved")

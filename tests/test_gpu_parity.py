@@ -235,8 +235,9 @@ def test_maximum_sizes_many_requests_and_one_very_long_request():
     # Sizes beyond every workload: 16384 requests of 0-64 tokens (the in-kernel
     # plan reads the lengths in 16 rounds of 1024 requests; most pairs are one
     # block), then one request of 131072 tokens at group 8 (8192 blocks per
-    # pair, every slice of the default plan inside one of its 8 pairs, cut
-    # pairs merged with ~128 contributors each). Every row against the oracle.
+    # pair; 32 workgroups for each of its 8 pairs, and with the VALU family every
+    # planned slice inside one pair, whose ~128 contributors are merged). Every
+    # row against the oracle.
     rng = np.random.default_rng(51)
     lens = rng.integers(0, 65, 16384)
     lens[rng.random(16384) < 0.05] = 0

@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import paper_2411_01142_amd as neo
+from division_cases import DIVISION_CASES, division_case
 from paper_2411_01142_amd import workloads as W
 
 torch = pytest.importorskip("torch")
@@ -92,6 +93,25 @@ def test_noalloc_with_interleaved_caches():
           f"bit-identical to the workspace entry={np.array_equal(got, want)}", flush=True)
     assert ae <= ABS_TOL and re <= REL_TOL
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("name", list(DIVISION_CASES))
+def test_noalloc_in_every_division(name):
+    # The static scratch in place of a workspace, whatever divides the call: the
+    # workspace entry point's bits, twice, with the other divisions' contents in
+    # the scratch.
+    lib = neo.load_library()
+    case = division_case(name)
+    print(f"[noalloc] {name}: B={case.batch} Hq={case.num_q_heads} Hkv={case.num_kv_heads}",
+          flush=True)
+    ws = neo.new_workspace(case.batch, case.num_q_heads, case.num_kv_heads)
+    want = _call(lib, case, "workspace", ws)
+    for _ in range(2):
+        got = _call(lib, case, "noalloc")
+        assert np.all(np.isfinite(got))
+        assert np.array_equal(got, want)
+    ae, re = _errors(got, oracle.decode_attention(case))
+    assert ae <= ABS_TOL and re <= REL_TOL
 
 
 def test_noalloc_repeated_calls_are_bit_identical():
