@@ -74,6 +74,17 @@ def kernel_source_sha(variant: str) -> str:
     return h.hexdigest()[:16]
 
 
+def kernel_name(neo, case, variant: str, schedule: str, max_slices: int,
+                compute_units: int) -> str:
+    """The decode kernel that a call of ``case`` launches, and how it divides the work."""
+    division = neo.debug_division(case.batch, case.num_q_heads, case.num_kv_heads,
+                                  case.max_blocks_per_seq, variant=variant,
+                                  max_slices=max_slices, compute_units=compute_units)
+    kernel = {"pairs": "decode_pair_kernel", "units": "decode_unit_kernel",
+              "whole": "decode_whole_kernel"}.get(division, f"decode_{variant}_kernel")
+    return f"{kernel}<{case.group}> ({division}, {schedule})"
+
+
 def load_traffic(workload_key: str, variant: str, launches_per_step: int = 1,
                  reads_only: bool = False):
     """HBM bytes per decode launch (read + written, or read only) from committed
@@ -860,7 +871,8 @@ def main(argv=None):
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": f"decode {resolved}, group {case.group}, {schedule}",
+            "kernel": kernel_name(neo, case, resolved, schedule, args.max_slices,
+                                  torch.cuda.get_device_properties(0).multi_processor_count),
             "achieved": round(achieved, 2),
             "peak": PEAK_HBM_GBS,
             "unit": "GB/s",

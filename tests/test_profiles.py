@@ -34,6 +34,24 @@ def test_counters_were_taken_on_the_current_kernel(path):
 
 
 @pytest.mark.parametrize("path", COUNTERS, ids=[os.path.basename(p) for p in COUNTERS])
+def test_counters_are_of_the_kernel_that_the_workload_takes(path):
+    import bench
+    import paper_2411_01142_amd as neo
+    from paper_2411_01142_amd import workloads as W
+    key = os.path.basename(path)[len("counters__decode_mfma_fused__"):-len(".md")]
+    cfg = next(c for c, spec in W.CONFIGS.items() if spec["name"] == key)
+    spec, lens = W.CONFIGS[cfg], W.config_seq_lens(cfg, cfg)
+
+    class Shapes:
+        batch, num_q_heads, num_kv_heads = len(lens), spec["num_q_heads"], spec["num_kv_heads"]
+        group = num_q_heads // num_kv_heads
+        max_blocks_per_seq = (int(lens.max()) + 15) // 16
+
+    name = bench.kernel_name(neo, Shapes, "mfma", "fused", 0, 256)
+    assert f"{name.split('<')[0]}<{Shapes.group}" in _record(path)["kernel"]
+
+
+@pytest.mark.parametrize("path", COUNTERS, ids=[os.path.basename(p) for p in COUNTERS])
 def test_counted_traffic_is_close_to_the_algorithmic_bytes(path):
     rec = _record(path)
     ratio = rec["traffic_bytes_per_launch"] / rec["algorithmic_bytes_per_launch"]
