@@ -297,14 +297,14 @@ __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_unit_kernel(
   unit_driver<MfmaFamily<G>, G, kSets>(p);
 }
 
-template <int G, bool kTwoRounds, int kSets>
+template <int G, bool kRounds, int kSets>
 __global__ __launch_bounds__(kWave * kPairWaves, 1) void decode_whole_kernel(
     const int32_t* __restrict__ lens, int32_t batch, int32_t hkv, int32_t mbps, DecodeParams p) {
   p.lens = lens;
   p.batch = batch;
   p.hkv = hkv;
   p.mbps = mbps;
-  whole_driver<MfmaFamily<G>, G, kTwoRounds, kSets>(p);
+  whole_driver<MfmaFamily<G>, G, kRounds, kSets>(p);
 }
 
 template <int G, int kSets>
@@ -354,8 +354,9 @@ hipError_t launch_mode(const DecodeParams& p, SliceMode mode, Schedule sched, in
     return hipGetLastError();
   }
   if (mode == kWhole) {
-    return p.batch <= kWave ? launch_whole<G, 1>(p, stream)
-                            : launch_whole<G, kWholeSets>(p, stream);
+    return p.batch <= kWave       ? launch_whole<G, 1>(p, stream)
+           : p.batch <= 2 * kWave ? launch_whole<G, 2>(p, stream)
+                                  : launch_whole<G, kWholeSets>(p, stream);
   }
   return mode == kHeadSlices ? launch_g<G, kHeadSlices>(p, sched, grid, stream)
                              : launch_g<G, kWaveSlices>(p, sched, grid, stream);

@@ -36,7 +36,8 @@
 //    of U[75, 150] 31.3 -> 13.6. (Fixed workgroups for every pair: 14.9, 4.9,
 //    30.5 and 23.9.)
 //  kWhole: 64 of U[512, 2048] 58 -> 51, 64 of 2048 tokens 89 -> 82, 32 of
-//    U[100, 1000] 19.7 -> 15.5; 512 of U[256, 4096] with 8 / 1 heads 102 -> 90.
+//    U[100, 1000] 19.7 -> 15.5, 96 of U[500, 3000] 114 -> 105; 512 of U[256,
+//    4096] with 8 / 1 heads 102 -> 90.
 //    Where it takes wave slices: one of 4096 among 64 of U[75, 150] 20.7 -> 20.7
 //    (whole pairs 41.6), 64 lognormal around 500 33.9 -> 33.8 (44.2).
 #pragma once
@@ -370,15 +371,19 @@ __device__ inline void unit_driver(const DecodeParams& p) {
                   v * p.hkv + g, [&](int32_t i) { return (u.unit0 + i) * p.hkv + g; }, lane, wv);
 }
 
-// kWhole: one workgroup per pair, longest first where they run in two rounds,
+// kWhole: one workgroup per pair, longest first where they run in rounds,
 // so that short ones fill the ends (index order / longest first: 64 requests of
 // U[512, 2048] tokens, 8 kv heads 57.7 / 55.9 us, 40 of them 41.3 / 35.9).
 constexpr int kLengthClasses = 16;
 constexpr int kWholeSets = kWholeMaxBatch / kWave;  // of 64 requests
-// Of kLoneBlocks, what remains where pairs follow each other on a compute unit:
+// Of kLoneBlocks, what remains where two pairs follow each other on a compute unit:
 // a second start costs about 3 us (264 pairs of 32 blocks each, an even share of
 // 33: 21.8 us whole, 19.4 in wave slices).
 constexpr float kLoneBlocksTwoRounds = 12.f;
+// Three rounds are three starts, worth it from this even share on (96 requests of
+// U[50, 150] tokens, 20 blocks a compute unit: 16.5 us in wave slices, 16.8 turned
+// to them; of 500 tokens, 96 blocks: 39.5 and 36.6).
+constexpr float kEvenBlocksThreeRounds = 32.f;
 
 // The request of rank r, longest first to within a sixteenth of the longest
 // (ties in index order): a ballot for each of 16 classes, a scan over the
@@ -435,7 +440,7 @@ __device__ inline int32_t request_of_rank(const DecodeParams& p, int32_t r, int3
   }
 }
 
-template <class F, int G, bool kTwoRounds, int kSets>
+template <class F, int G, bool kRounds, int kSets>
 __device__ inline void whole_driver(const DecodeParams& p) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = uniform(threadIdx.x >> 6);
@@ -450,7 +455,7 @@ __device__ inline void whole_driver(const DecodeParams& p) {
   // the lengths.
   int32_t b = min(r, p.batch - 1), ids = 0;
   typename F::Q q;
-  if constexpr (!kTwoRounds) {
+  if constexpr (!kRounds) {
     ids = p.table[(size_t)b * p.mbps + min(block_of(lane), p.mbps - 1)];
     F::load_q(q, p.q + ((size_t)b * p.hq + g * G) * kHeadDim, lane);
   }
@@ -469,19 +474,25 @@ __device__ inline void whole_driver(const DecodeParams& p) {
   const int32_t longest = wave_max_i32(most);
   const float even = (float)wave_sum_i32(sum) * (float)p.hkv / (float)p.cus;
   bool whole = (float)longest <= even + lone_slack<G>(p, even, W, longest);
-  if constexpr (kTwoRounds) {
+  if constexpr (kRounds) {
     // Two pairs of more than half of what a compute unit may have must not follow
-    // each other on one.
-    const float half = 0.5f * (even + kLoneBlocksOfEven * even + kLoneBlocksTwoRounds);
-    int32_t halves = 0;
+    // each other on one, nor three of more than a third.
+    const int32_t pairs = p.batch * p.hkv;
+    const bool two = pairs <= 2 * p.cus;
+    const float may = even + kLoneBlocksOfEven * even + (two ? kLoneBlocksTwoRounds : 0.f);
+    for (int32_t k = 1; k * p.cus < pairs; ++k) {
+      int32_t larger = 0;
 #pragma unroll
-    for (int t = 0; t < kSets; ++t) halves += __popcll(__ballot((float)nb[t] > half));
-    whole = whole && halves * p.hkv <= p.cus;
+      for (int t = 0; t < kSets; ++t)
+        larger += __popcll(__ballot((float)nb[t] * (float)(k + 1) > may));
+      whole = whole && larger * p.hkv <= k * p.cus;
+    }
+    whole = whole && (two || even >= kEvenBlocksThreeRounds);
   }
   if (uniform(whole)) {
     if (r >= p.batch) return;
     int32_t len;
-    if constexpr (kTwoRounds) {
+    if constexpr (kRounds) {
       // (Short pairs are not worth an order: 64 requests of U[50, 150] tokens 9.7
       // us in index order, 11.7 longest first.)
       if (longest > kPairShortBlocks)

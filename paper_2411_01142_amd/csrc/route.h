@@ -25,29 +25,32 @@ struct Route {
 // Times below: device time of a call with 32 / 8 heads on 256 compute units,
 // tables as wide as the longest request where no width is given.
 //
-// Without slices: up to two (request, kv head) pairs per compute unit. With more
-// of them short pairs lose (in planned slices / one workgroup per pair: 64
-// requests of U[50, 150] tokens, two pairs per compute unit, 13.3 / 9.6 us; 128,
-// four, 16.6 / 17.0, and 18.3 in tables of 200 columns, where the device has to
-// choose). Long ones would gain (128 of U[500, 3000] 147 / 138, of 500 tokens 47.4
-// / 48.1; 512 requests of two kv heads 155 / 150 and 50.5 / 55.0).
-constexpr int32_t kPairsPerCu = 2;
+// Without slices: up to three (request, kv head) pairs per compute unit (in
+// planned slices / so: 96 requests of U[50, 150] tokens 16.5 / 13.3 us, of U[500,
+// 3000] 114 / 105, of 500 tokens in 200 columns 39.6 / 36.5). Of a batch that it
+// reads, the kernel reads 64 lengths a register of every wavefront, and for three
+// rounds of workgroups that is worth it up to kThreeRoundsMaxBatch requests (300
+// of 500 tokens, two kv heads, 37.3 / 39.7). With four, short pairs lose where
+// the device has to choose (128 requests of U[50, 150], 200 columns, 16.4 / 18.3;
+// of U[500, 3000] 147 / 138).
+constexpr int32_t kPairsPerCu = 3;
+constexpr int32_t kThreeRoundsMaxBatch = 2 * kWave;
+//
 // A pair of at most kPairShortBlocks blocks is not worth a merge (19 blocks: 6.8
-// us by one workgroup, 8.3 by two), and any batch of such pairs is a good one.
-// kPairs beyond that: one request, whose pairs are equal, at any width; and
-// while a workgroup has at most as many blocks of the longest pair there may
-// be. Then the lengths are not worth a round trip (5 requests of U[50, 150]
-// tokens: 4.9 us so, 5.6 in units; 13 of U[100, 1500], at most 47 blocks: 13.2
-// so, 12.3 in units). Where pairs outnumber half of the compute units none is
-// cut, and a lone one of twice as many costs less than the round trip (32 of
-// U[50, 150]: 6.0 so, 5.9-6.6 as kWhole).
+// us by one workgroup, 8.3 by two), and any batch of such pairs suits kPairs.
+// Wider tables take it where a workgroup still has at most that many blocks (5
+// requests of U[50, 150] tokens: 4.9 us so, 5.6 as kUnits, whose lengths are a
+// round trip more; 13 of U[100, 1500], up to 47 blocks each: 13.2 and 12.3), or
+// twice as many where pairs outnumber half of the compute units, so that none
+// can be cut (32 of U[50, 150]: 6.0 so, 6.6 as kWhole); and with one request,
+// whose pairs are equal.
 //
-// Cutting needs compute units to spare: up to half of them taken, units of at
-// most twice an even share of the blocks are enough (kUnits). With more pairs
+// Cutting needs compute units to spare: with up to half of them taken, units of
+// at most twice an even share of the blocks are enough (kUnits). With more pairs
 // none is cut (kWhole).
-//
 constexpr int32_t kMaxCus = 256;
-static_assert(kPairsPerCu * kMaxCus <= kWholeMaxBatch && kMaxCus / 2 <= kUnitMaxBatch,
+static_assert(2 * kMaxCus <= kWholeMaxBatch && kThreeRoundsMaxBatch <= kWholeMaxBatch &&
+                  kMaxCus / 2 <= kUnitMaxBatch,
               "the kernels read that many lengths");
 
 // Head slices need whole groups of four kv heads, and pay once every compute
@@ -76,7 +79,8 @@ inline Route route(int32_t variant, int32_t max_slices, int32_t batch, int32_t h
                    int32_t cus) {
   if (variant != NEO_VARIANT_MFMA || max_slices != 0) return {kWaveSlices, 0, 0, 0};
   const int64_t pairs = (int64_t)batch * hkv;
-  if (pairs <= (int64_t)kPairsPerCu * cus && cus <= kMaxCus) {
+  if (pairs <= (int64_t)kPairsPerCu * cus && cus <= kMaxCus &&
+      (pairs <= 2 * (int64_t)cus || batch <= kThreeRoundsMaxBatch || mbps <= kPairShortBlocks)) {
     const int32_t n = (int32_t)pairs;
     const bool uncut = n > cus / 2;
     if (mbps <= kPairShortBlocks || (uncut && n <= cus && mbps <= 2 * kPairShortBlocks))

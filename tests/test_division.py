@@ -13,7 +13,8 @@ WIDE = (200, 256, 257, 512, 2048, 8192)
     (13, 8, "units"), (4, 32, "units"), (16, 8, "units"), (128, 1, "units"), (40, 1, "units"),
     (13, 3, "units"), (1, 8, "pairs"), (1, 1, "pairs"), (1, 128, "pairs"),
     (256, 8, "head_slices"), (512, 8, "head_slices"), (1024, 8, "head_slices"),
-    (65, 8, "wave_slices"), (200, 8, "wave_slices"), (513, 1, "wave_slices"),
+    (65, 8, "whole"), (96, 8, "whole"), (128, 6, "whole"), (97, 8, "wave_slices"),
+    (129, 5, "wave_slices"), (200, 8, "wave_slices"), (513, 1, "wave_slices"),
     (1024, 1, "wave_slices"), (2048, 1, "wave_slices"), (171, 3, "wave_slices")])
 def test_room_in_the_table_does_not_change_the_division(batch, hkv, want):
     got = {w: neo.debug_division(batch, 4 * hkv, hkv, w) for w in WIDE}
@@ -22,9 +23,10 @@ def test_room_in_the_table_does_not_change_the_division(batch, hkv, want):
 
 def test_tables_of_short_pairs_and_small_shares():
     d = neo.debug_division
-    # At most 32 blocks a pair, up to two pairs per compute unit.
+    # At most 32 blocks a pair, up to three pairs per compute unit.
     assert d(64, 32, 8, 32) == "pairs" and d(64, 32, 8, 33) == "whole"
-    assert d(65, 32, 8, 32) == "wave_slices"
+    assert d(96, 32, 8, 32) == "pairs" and d(97, 32, 8, 32) == "wave_slices"
+    assert d(768, 8, 1, 32) == "pairs" and d(768, 8, 1, 33) == "wave_slices"
     assert d(4, 32, 32, 32) == "pairs" and d(4, 32, 32, 33) == "pairs"
     # One workgroup a pair of at most 64 blocks where none can be cut.
     assert d(32, 32, 8, 64) == "pairs" and d(32, 32, 8, 65) == "whole"

@@ -73,6 +73,13 @@ CASES = {
     "whole_rounds_bad": (8, [4096] + [150] * 61 + [0, 1], 0),
     "whole_rounds_halves": (8, [2048] * 33, 0),
     "whole_rounds_none": (8, [0] * 40, 60),
+    "whole_three_rounds": (8, [(i * 353) % 1537 + 256 for i in range(94)] + [0, 1], 30),
+    "whole_three_rounds_128": (6, [(i * 353) % 900 + 100 for i in range(128)], 0),
+    "whole_three_rounds_short": (8, [(i * 37) % 200 for i in range(90)], 60),
+    "whole_three_rounds_bad": (8, [4096] + [150] * 80, 0),
+    "whole_three_rounds_thirds": (8, [512] * 65, 20),
+    "pairs_three_rounds": (8, [(i * 37) % 513 for i in range(96)], 0),
+    "pairs_768": (1, [(i * 37) % 500 for i in range(768)], 0),
 }
 
 
