@@ -38,7 +38,7 @@ def _lens(kind, batch, rng):
         x = 16 * rng.integers(0, 60, batch)
     elif kind == "runs":    # runs of empty requests longer than a wavefront
         x = np.where(np.arange(batch) % 90 < 3, rng.integers(1200, 3000, batch), 0)
-    elif kind == "ones":    # one block each: hundreds of requests in a slice
+    elif kind == "ones":    # one block each: more than 64 requests in a slice
         x = rng.integers(1, 17, batch)
         x[5] = 600
     else:                   # a few requests over many slices, between short ones
@@ -56,7 +56,7 @@ def test_head_slices_match_the_oracle(group, kind):
     batch = 2048 // hkv + 3  # more than two pairs of four heads per compute unit
     batch *= 4 if hkv == 4 else 1
     if kind in ("runs", "ones"):
-        hkv, batch = 4, 12000 if kind == "ones" else 1800
+        hkv, batch = 4, 18000 if kind == "ones" else 1800
     _check(group, hkv, _lens(kind, batch, rng), kind, extra=3)
 
 
